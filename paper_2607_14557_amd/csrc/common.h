@@ -98,6 +98,38 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblk) {
   return bid < (per << 3) ? (bid & 7) * per + (bid >> 3) : bid;
 }
 
+// Tile j of the batch's row tiles (ceil(len_b / qt) tiles of qt rows per
+// sequence, in sequence order): its sequence b and its index t there.  False
+// past the last tile.  Called by whole waves: 64 sequences are counted at a
+// time with one wave-wide prefix sum.
+__device__ __forceinline__ bool tile_of(const int* cu, int B, int qt, int j, int& b, int& t) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int acc = 0;
+  for (int s0 = 0; s0 < B; s0 += kWave) {
+    const int s = s0 + lane;
+    int nt = 0;
+    if (s < B) {
+      const int len = cu[s + 1] - cu[s];
+      nt = len > 0 ? (len + qt - 1) / qt : 0;
+    }
+    int inc = nt;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int v = __shfl_up(inc, off, kWave);
+      if (lane >= off) inc += v;
+    }
+    const unsigned long long hit = __ballot(j < acc + inc);
+    if (hit) {
+      const int f = __builtin_ctzll(hit);
+      b = s0 + f;
+      t = j - acc - __builtin_amdgcn_readlane(inc - nt, f);
+      return true;
+    }
+    acc += __builtin_amdgcn_readlane(inc, kWave - 1);
+  }
+  return false;
+}
+
 // Row count of a packed batch: cu_seqlens[batch] when given, clamped to the
 // host-side upper bound that sized the grid.
 __device__ __forceinline__ int rows_from(const int* m_ptr, int m_ub) {

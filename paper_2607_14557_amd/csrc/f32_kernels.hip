@@ -1,6 +1,6 @@
 // fp32 variants of the layer kernels (any d_model, d_ff; head_dim <= 128).
 //
-// These serve the small fp32 layer shape; they are plain vector-ALU kernels
+// These serve the small fp32 layer shape; they are vector-ALU kernels
 // (LDS-tiled GEMM with the same fused epilogues as the bf16 path, and a
 // one-query-per-lane online-softmax attention) and are not performance
 // critical.
@@ -111,49 +111,68 @@ int launch_gemm_f32(int epi, const GemmParams& p, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// ---------------------------------------------------------------------------
-// fp32 attention: one query per lane, 64 queries per workgroup, keys staged in
-// LDS 32 at a time, online softmax per query.
 namespace {
-constexpr int AQ = 64;
-constexpr int AK = 32;
+
+template <int N>
+struct FVec { float v[N]; };
+
+// N consecutive floats at src + c of a row of `n` valid ones, zero past n.
+template <int N, bool VEC>
+__device__ __forceinline__ FVec<N> load_chunk(const float* src, int c, int n) {
+  FVec<N> r;
+  if constexpr (VEC) {
+    // n % 4 == 0 and c is a multiple of N: the chunk is all in or all out
+    typedef float vec_t __attribute__((ext_vector_type(N)));
+    const vec_t x = *reinterpret_cast<const vec_t*>(src + (c < n ? c : 0));
+#pragma unroll
+    for (int e = 0; e < N; ++e) r.v[e] = c < n ? x[e] : 0.0f;
+  } else {
+#pragma unroll
+    for (int e = 0; e < N; ++e) r.v[e] = c + e < n ? src[c + e] : 0.0f;
+  }
+  return r;
 }
 
-template <int DH>
-__global__ __launch_bounds__(AQ) void attn_f32_kernel(AttnParams p) {
-  __shared__ float ks[AK][DH];
-  __shared__ float vs[AK][DH];
-  int b = -1, t = 0;
-  {
-    int acc = 0;
-    for (int s = 0; s < p.B; ++s) {
-      int len = p.cu[s + 1] - p.cu[s];
-      len = len < 0 ? 0 : len;
-      const int nt = (len + AQ - 1) / AQ;
-      if ((int)blockIdx.x < acc + nt) { b = s; t = blockIdx.x - acc; break; }
-      acc += nt;
-    }
-  }
-  if (b < 0) return;
+}  // namespace
+
+// ---------------------------------------------------------------------------
+// fp32 attention, one workgroup per (sequence, 16 queries, head).  The batches
+// are small, so a launch is bound by the length of one workgroup's chain, not
+// by throughput: its four waves take a quarter of the keys each, with an
+// online softmax of their own, and merge through LDS at the end.
+//
+// Scores are computed transposed, S^T = K Q^T, so register r of a 16-key tile
+// holds query lane%16 and key 4 (lane/16) + r, which is already the operand
+// layout of O^T = V^T P^T: no shuffle of P.  K, Q and V come straight from
+// memory (the rows of one head fit L2), 16 bytes per lane: lane group lane/16
+// takes dims 16 j + 4 (lane/16) .. +3 of a chunk for four MFMAs, and output
+// tile (g, e) holds the dims 16 E g + E i + e, i < 16.
+//
+// Measured against one lane per query walking every key: one 224-row sequence
+// of 4 heads of 64, 327 -> 10 us; 16 sequences of 105-224 rows, 330 -> 22 us.
+// 32 queries per workgroup (half the K and V loads per query) took 26 us there
+// and 349 against 313 us at 11,600 rows of 8 heads: fewer waves per SIMD.
+//
+// VEC: 16-byte loads (head_dim % 4 == 0 and aligned rows); otherwise the same
+// chunks element by element.
+template <int DH, bool VEC>
+__global__ __launch_bounds__(256) void attn_f32_kernel(AttnParams p) {
+  constexpr int QT = 16;
+  constexpr int NJ = DH / 16;                 // 16-dim chunks of a head
+  constexpr int E = NJ < 4 ? NJ : 4;          // dims per V load and lane
+  constexpr int G = NJ / E;
+  __shared__ float s_o[4][QT][DH + 4];
+  __shared__ float s_m[4][QT], s_l[4][QT];
+  int b, t;
+  if (!tile_of(p.cu, p.B, QT, blockIdx.x, b, t)) return;
   const int h = blockIdx.y;
   const int s0 = p.cu[b];
   if (s0 < 0 || s0 >= p.rows_ub) return;
   int len = p.cu[b + 1] - s0;
   len = len > p.rows_ub - s0 ? p.rows_ub - s0 : len;
-  if (t * AQ >= len) return;
+  if (t * QT >= len) return;
   int used = p.used ? p.used[b] : len;
   used = used < 0 ? 0 : (used > len ? len : used);
-  const float* qkv = static_cast<const float*>(p.qkv);
-  float* out = static_cast<float*>(p.out);
-  const size_t ld = (size_t)3 * p.d;
-  const int q_row = t * AQ + threadIdx.x;
-  const int q_src = q_row < len ? q_row : len - 1;
-  float q[DH], o[DH];
-#pragma unroll
-  for (int e = 0; e < DH; ++e) {
-    q[e] = e < p.head_dim ? qkv[(size_t)(s0 + q_src) * ld + h * p.head_dim + e] * p.scale : 0.0f;
-    o[e] = 0.0f;
-  }
   // keys: the cached prefix rows (if any), then the sequence's own used rows
   int P = 0, kv0 = 0;
   if (p.cu_kv) {
@@ -161,53 +180,173 @@ __global__ __launch_bounds__(AQ) void attn_f32_kernel(AttnParams p) {
     P = p.cu_kv[b + 1] - kv0;
     P = P < 0 ? 0 : P;
   }
-  const int n_keys = P + used;
-  const float* kvc = static_cast<const float*>(p.kv);
+  const int nk = P + used;
+
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int li = lane & 15, lq = lane >> 4;
+  const int hd = p.head_dim;
+  const size_t ld = (size_t)3 * p.d;
+  const float* qkv = static_cast<const float*>(p.qkv) + h * hd;
+  const float* kvc = p.cu_kv ? static_cast<const float*>(p.kv) + h * hd : nullptr;
+  // K row of key position k < nk; its V row is d elements further
+  auto key_row = [&](int k) {
+    return k < P ? kvc + (size_t)(kv0 + k) * 2 * p.d : qkv + (size_t)(s0 + k - P) * ld + p.d;
+  };
+
+  f32x4_t qf[NJ];
+  {
+    int q = t * QT + li;
+    q = q < len ? q : len - 1;
+    const float* qr = qkv + (size_t)(s0 + q) * ld;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const FVec<4> c = load_chunk<4, VEC>(qr, 16 * j + 4 * lq, hd);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) qf[j][e] = c.v[e] * p.scale;
+    }
+  }
+  f32x4_t o[NJ];
   float m = -INFINITY, l = 0.0f;
-  for (int k0 = 0; k0 < n_keys; k0 += AK) {
-    for (int e = threadIdx.x; e < AK * DH; e += AQ) {
-      const int kk = e / DH, c = e % DH;
-      const int key = k0 + kk;
-      const bool ok = key < n_keys && c < p.head_dim;
-      const float* kr = !ok ? nullptr
-          : key < P ? kvc + (size_t)(kv0 + key) * 2 * p.d + h * p.head_dim + c
-                    : qkv + (size_t)(s0 + key - P) * ld + p.d + h * p.head_dim + c;
-      ks[kk][c] = ok ? kr[0] : 0.0f;
-      vs[kk][c] = ok ? kr[p.d] : 0.0f;
-    }
-    __syncthreads();
-    const int nk = min(AK, n_keys - k0);
-    for (int kk = 0; kk < nk; ++kk) {
-      float sc = 0.0f;
 #pragma unroll
-      for (int e = 0; e < DH; ++e) sc = fmaf(q[e], ks[kk][e], sc);
-      const float mn = fmaxf(m, sc);
-      const float alpha = __expf(m - mn);
-      const float pe = __expf(sc - mn);
-      l = l * alpha + pe;
+  for (int j = 0; j < NJ; ++j) o[j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // This wave's keys: a quarter of the 16-key tiles, walked two at a time.  A
+  // step's V is requested before its scores and the next step's K before its
+  // softmax, so that neither latency is on the chain.
+  const int per = ((nk + 15) / 16 + 3) / 4;
+  const int k_begin = 16 * per * wave, k_end = min(k_begin + 16 * per, nk);
+  FVec<4> kf[2][NJ];
+  FVec<E> vf[2][4][G];
+  auto load_k = [&](int k0) {
 #pragma unroll
-      for (int e = 0; e < DH; ++e) o[e] = fmaf(pe, vs[kk][e], o[e] * alpha);
-      m = mn;
+    for (int c = 0; c < 2; ++c) {
+      const int key = k0 + 16 * c + li;
+      const float* kr = key_row(key < nk ? key : nk - 1);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) kf[c][j] = load_chunk<4, VEC>(kr, 16 * j + 4 * lq, hd);
     }
-    __syncthreads();
+  };
+  if (k_begin < k_end) load_k(k_begin);
+  for (int k0 = k_begin; k0 < k_end; k0 += 32) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int key = k0 + 16 * c + 4 * lq + r;
+        const float* vr = key_row(key < nk ? key : nk - 1) + p.d;
+#pragma unroll
+        for (int g = 0; g < G; ++g) vf[c][r][g] = load_chunk<E, VEC>(vr, 16 * E * g + E * li, hd);
+      }
+    f32x4_t s[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      s[c] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          s[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][j].v[e], qf[j][e], s[c], 0, 0, 0);
+    }
+    if (k0 + 32 < k_end) load_k(k0 + 32);
+    if (k0 + 32 > k_end) {
+      // masked keys: probability 0, and a zero V so that they add 0 x 0
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (k0 + 16 * c + 4 * lq + r >= k_end) {
+            s[c][r] = -INFINITY;
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+              for (int e = 0; e < E; ++e) vf[c][r][g].v[e] = 0.0f;
+          }
+    }
+    // the four lane groups of a query hold 8 of the step's 32 keys each; key
+    // k0 is never masked, so the step's maximum covers a real score
+    float mt = s[0][0];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) mt = fmaxf(mt, s[c][r]);
+    mt = fmaxf(mt, __shfl_xor(mt, 16, kWave));
+    mt = fmaxf(mt, __shfl_xor(mt, 32, kWave));
+    const float mn = fmaxf(m, mt);
+    const float alpha = __expf(m - mn);
+    m = mn;
+    l *= alpha;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) o[j] *= alpha;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float pe = __expf(s[c][r] - mn);
+        s[c][r] = pe;
+        l += pe;
+      }
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < E; ++e)
+            o[g * E + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][r][g].v[e], s[c][r], o[g * E + e], 0, 0, 0);
   }
-  if (q_row < len) {
-    const float inv = (q_row < used && l > 0.0f) ? 1.0f / l : 0.0f;
-    for (int e = 0; e < p.head_dim; ++e)
-      out[(size_t)(s0 + q_row) * p.d + h * p.head_dim + e] = o[e] * inv;
+
+  // merge the four waves' states in wave order
+  l += __shfl_xor(l, 16, kWave);
+  l += __shfl_xor(l, 32, kWave);
+  if (lq == 0) {
+    s_m[wave][li] = m;
+    s_l[wave][li] = l;
   }
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s_o[wave][li][16 * E * g + E * (4 * lq + r) + e] = o[g * E + e][r];
+  __syncthreads();
+  float* out = static_cast<float*>(p.out);
+  for (int i = threadIdx.x; i < QT * DH; i += 256) {
+    const int q = i / DH, c = i % DH;
+    const int q_row = t * QT + q;
+    if (q_row >= len || c >= hd) continue;
+    float mx = s_m[0][q];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) mx = fmaxf(mx, s_m[w][q]);
+    float num = 0.0f, den = 0.0f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      // a wave without keys (m = -inf, l = 0) adds nothing
+      const float f = s_l[w][q] == 0.0f ? 0.0f : __expf(s_m[w][q] - mx);
+      num = fmaf(f, s_o[w][q][c], num);
+      den = fmaf(f, s_l[w][q], den);
+    }
+    const float inv = (q_row < used && den > 0.0f) ? 1.0f / den : 0.0f;
+    out[(size_t)(s0 + q_row) * p.d + h * hd + c] = num * inv;
+  }
+}
+
+template <int DH>
+static void launch_attn_f32_dh(const AttnParams& p, bool vec, hipStream_t s) {
+  dim3 grid((p.rows_ub + 15) / 16 + p.B, p.n_heads), block(256);
+  if (vec) hipLaunchKernelGGL((attn_f32_kernel<DH, true>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((attn_f32_kernel<DH, false>), grid, block, 0, s, p);
 }
 
 int launch_attn_f32(const AttnParams& p, hipStream_t s) {
   if (p.cu_kv && !p.kv) return -1;
-  dim3 grid((p.rows_ub + AQ - 1) / AQ + p.B, p.n_heads), block(AQ);
-  if (p.head_dim <= 64) {
-    hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, s, p);
-  } else if (p.head_dim <= 128) {
-    hipLaunchKernelGGL(attn_f32_kernel<128>, grid, block, 0, s, p);
-  } else {
-    return -1;
-  }
+  auto a16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+  const bool vec = p.head_dim % 4 == 0 && p.d % 4 == 0 && a16(p.qkv) && (!p.cu_kv || a16(p.kv));
+  if (p.head_dim <= 32) launch_attn_f32_dh<32>(p, vec, s);
+  else if (p.head_dim <= 64) launch_attn_f32_dh<64>(p, vec, s);
+  else if (p.head_dim <= 128) launch_attn_f32_dh<128>(p, vec, s);
+  else return -1;
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
