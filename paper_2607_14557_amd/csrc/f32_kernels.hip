@@ -1,115 +1,13 @@
-// fp32 variants of the layer kernels (any d_model, d_ff; head_dim <= 128).
-//
-// These serve the small fp32 layer shape; they are vector-ALU kernels
-// (LDS-tiled GEMM with the same fused epilogues as the bf16 path, and a
-// one-query-per-lane online-softmax attention) and are not performance
-// critical.
+// fp32 variants of the layer kernels (any d_model, d_ff; head_dim <= 128): the
+// GEMM with the same fused epilogues as the bf16 path, attention and the
+// rotary embedding, on the fp32 matrix instruction (16x16x4: exact products,
+// fp32 sums).
 #include <math.h>
 
 #include "common.h"
 #include "kernels.h"
 
 namespace seer {
-
-namespace {
-constexpr int TM = 64, TN = 64, TK = 16;
-}
-
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
-  constexpr bool kGlu = (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_COUNT);
-  __shared__ float As[TK][TM + 4];
-  __shared__ float Bs[TK][TN + 4];
-  __shared__ float B2s[kGlu ? TK : 1][TN + 4];
-  const int M = rows_from(p.m_ptr, p.m_ub);
-  const int m0 = blockIdx.y * TM;
-  const int n0 = blockIdx.x * TN;
-  if (m0 >= M) return;
-  const float* A = static_cast<const float*>(p.A);
-  const float* Bm = static_cast<const float*>(p.B);
-  const float* B2 = static_cast<const float*>(p.B2);
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  float acc[4][4], acc2[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { acc[i][j] = 0.0f; acc2[i][j] = 0.0f; }
-
-  for (int k0 = 0; k0 < p.K; k0 += TK) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + 256 * i;
-      const int r = e >> 4, kk = e & 15;
-      const int gk = k0 + kk;
-      const int gr = m0 + r, gn = n0 + r;
-      As[kk][r] = (gr < M && gk < p.K) ? A[(size_t)gr * p.lda + gk] : 0.0f;
-      Bs[kk][r] = (gn < p.N && gk < p.K) ? Bm[(size_t)gn * p.ldb + gk] : 0.0f;
-      if constexpr (kGlu) B2s[kk][r] = (gn < p.N && gk < p.K) ? B2[(size_t)gn * p.ldb + gk] : 0.0f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      float a[4], b[4], b2[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        b[j] = Bs[kk][tx * 4 + j];
-        if constexpr (kGlu) b2[j] = B2s[kk][tx * 4 + j];
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-          if constexpr (kGlu) acc2[i][j] = fmaf(a[i], b2[j], acc2[i][j]);
-        }
-    }
-    __syncthreads();
-  }
-
-  float* C = static_cast<float*>(p.C);
-  const float* R = static_cast<const float*>(p.R);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = m0 + ty * 4 + i;
-    if (row >= M) continue;
-    int cnt = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = n0 + tx * 4 + j;
-      if (col >= p.N) continue;
-      float v;
-      if constexpr (EPI == EPI_SCALE) {
-        v = acc[i][j] * p.rs[row];
-      } else if constexpr (EPI == EPI_RESID) {
-        v = R[(size_t)row * p.ldr + col] + acc[i][j];
-      } else {
-        const float s = p.rs[row];
-        v = silu(acc[i][j] * s) * (acc2[i][j] * s);
-        cnt += fabsf(v) < p.eps ? 1 : 0;
-      }
-      C[(size_t)row * p.ldc + col] = v;
-    }
-    if constexpr (EPI == EPI_SWIGLU_COUNT) {
-      if (cnt) atomicAdd(p.cnt + row, cnt);
-    }
-  }
-}
-
-int launch_gemm_f32(int epi, const GemmParams& p, hipStream_t s) {
-  dim3 grid((p.N + TN - 1) / TN, (p.m_ub + TM - 1) / TM), block(256);
-  switch (epi) {
-    case EPI_SCALE: hipLaunchKernelGGL(gemm_f32_kernel<EPI_SCALE>, grid, block, 0, s, p); break;
-    case EPI_RESID: hipLaunchKernelGGL(gemm_f32_kernel<EPI_RESID>, grid, block, 0, s, p); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL(gemm_f32_kernel<EPI_SWIGLU>, grid, block, 0, s, p); break;
-    case EPI_SWIGLU_COUNT:
-      hipLaunchKernelGGL(gemm_f32_kernel<EPI_SWIGLU_COUNT>, grid, block, 0, s, p); break;
-    default: return -1;
-  }
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
 
 namespace {
 
@@ -134,6 +32,197 @@ __device__ __forceinline__ FVec<N> load_chunk(const float* src, int c, int n) {
 }
 
 }  // namespace
+
+// C[M,N] = A[M,K] B[N,K]^T.  A workgroup owns one square tile of 16 W rows and
+// columns; its four waves take a quarter of K each and sum through LDS in wave
+// order at the end.  Operands go straight from memory to registers, 16 bytes
+// per lane, one 16-wide K step ahead (the summed index of an MFMA may be
+// permuted freely, so lane group lane/16 takes K values k0 + 4 (lane/16) .. +3
+// for four MFMAs, and a load covers whole 64-byte runs of 16 rows): no LDS and
+// no barrier in the loop.  The weights are the first MFMA operand, so lane l
+// holds row l%16 and four consecutive columns 4 (l/16) .. +3 of a 16x16 tile.
+//
+// What bounds it: the chain of one wave (load, MFMAs, the LDS sum) while the
+// tiles fit the chip a few times over, hence the four-way K split and the
+// small tile; the operand loads from L2 beyond that.  Against a 64x64 LDS-tiled
+// vector-ALU kernel (d 256, d_ff 688, times in us for QKV / O / gate-up / down):
+// 224 rows 37 / 38 / 58 / 130 -> 6 / 5 / 8 / 9; 2668 rows 40 / 36 / 61 / 126 ->
+// 21 / 9 / 30 / 18.  Three K steps ahead instead of one: 30 -> 49 us on that
+// gate/up (the loads past a wave's short range are wasted).
+// VEC: 16-byte accesses (every row a multiple of 16 bytes, aligned bases).
+template <int EPI, int W, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
+  constexpr bool kGlu = (EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_COUNT);
+  constexpr int NB = kGlu ? 2 : 1;                  // B operands (gate and up)
+  constexpr int KS = 4;                             // waves, each a quarter of K
+  constexpr int TILE = 16 * W;
+  constexpr int CPT = W / 2;                       // 4-column groups per thread and 32-row part
+  __shared__ float s_acc[KS * NB][32][TILE + 4];
+  const int M = rows_from(p.m_ptr, p.m_ub);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int li = lane & 15, lq = lane >> 4;
+  const int m0 = blockIdx.y * TILE, n0 = blockIdx.x * TILE;
+  if (m0 >= M) return;
+  const float* ap[W];
+  const float* bp[NB][W];
+  // rows and columns past the matrix re-read the last one (never stored)
+#pragma unroll
+  for (int i = 0; i < W; ++i)
+    ap[i] = static_cast<const float*>(p.A) + (size_t)min(m0 + 16 * i + li, M - 1) * p.lda;
+#pragma unroll
+  for (int i = 0; i < W; ++i) {
+    const int c = min(n0 + 16 * i + li, p.N - 1);
+    bp[0][i] = static_cast<const float*>(p.B) + (size_t)c * p.ldb;
+    if constexpr (kGlu) bp[NB - 1][i] = static_cast<const float*>(p.B2) + (size_t)c * p.ldb;
+  }
+  f32x4_t acc[NB][W][W];
+#pragma unroll
+  for (int u = 0; u < NB; ++u)
+#pragma unroll
+    for (int i = 0; i < W; ++i)
+#pragma unroll
+      for (int j = 0; j < W; ++j) acc[u][i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // K steps of 16 [t0, t1) of this wave
+  const int steps = (p.K + 15) / 16;
+  const int per = (steps + KS - 1) / KS;
+  const int t0 = min(per * wave, steps), t1 = min(t0 + per, steps);
+  struct Frag { FVec<4> a[W], b[NB][W]; };
+  auto load = [&](int t, Frag& f) {
+    const int k = 16 * t + 4 * lq;
+#pragma unroll
+    for (int i = 0; i < W; ++i) f.a[i] = load_chunk<4, VEC>(ap[i], k, p.K);
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+#pragma unroll
+      for (int u = 0; u < NB; ++u) f.b[u][i] = load_chunk<4, VEC>(bp[u][i], k, p.K);
+    }
+  };
+  auto mul = [&](const Frag& f) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+#pragma unroll
+        for (int i = 0; i < W; ++i)
+#pragma unroll
+          for (int j = 0; j < W; ++j)
+            acc[u][i][j] =
+                __builtin_amdgcn_mfma_f32_16x16x4f32(f.b[u][j].v[e], f.a[i].v[e], acc[u][i][j], 0, 0, 0);
+  };
+  if (t0 < t1) {
+    Frag f0, f1;
+    load(t0, f0);
+    int t = t0;
+    for (; t + 2 < t1; t += 2) {
+      load(t + 1, f1);
+      mul(f0);
+      load(t + 2, f0);
+      mul(f1);
+    }
+    if (t + 1 < t1) {
+      load(t + 1, f1);
+      mul(f0);
+      mul(f1);
+    } else {
+      mul(f0);
+    }
+  }
+
+  float* C = static_cast<float*>(p.C);
+  const float* R = static_cast<const float*>(p.R);
+  // the tile in parts of 32 rows: partial sums to LDS, then thread t adds the
+  // waves' values of row t / 8 and 4-column groups t % 8 + 8 g
+#pragma unroll
+  for (int part = 0; part < W / 2; ++part) {
+    if (part) __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < W; ++j)
+          *reinterpret_cast<f32x4_t*>(&s_acc[wave * NB + u][16 * i + li][16 * j + 4 * lq]) = acc[u][2 * part + i][j];
+    __syncthreads();
+    const int r = threadIdx.x >> 3;
+    const int row = m0 + 32 * part + r;
+    int cnt = 0;
+#pragma unroll
+    for (int g = 0; g < CPT; ++g) {
+      const int c = 4 * ((threadIdx.x & 7) + 8 * g);
+      const int col = n0 + c;
+      if (row >= M || col >= p.N) continue;
+      f32x4_t sum[NB];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        sum[u] = *reinterpret_cast<const f32x4_t*>(&s_acc[u][r][c]);
+#pragma unroll
+        for (int w = 1; w < KS; ++w) sum[u] += *reinterpret_cast<const f32x4_t*>(&s_acc[w * NB + u][r][c]);
+      }
+      f32x4_t v = sum[0];
+      if constexpr (EPI == EPI_SCALE) v *= p.rs[row];
+      if constexpr (kGlu) {
+        const float sc = p.rs[row];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = silu(sum[0][e] * sc) * (sum[NB - 1][e] * sc);
+          if (EPI == EPI_SWIGLU_COUNT && col + e < p.N) cnt += fabsf(v[e]) < p.eps ? 1 : 0;
+        }
+      }
+      float* dst = C + (size_t)row * p.ldc + col;
+      if constexpr (VEC) {
+        if constexpr (EPI == EPI_RESID) v += *reinterpret_cast<const f32x4_t*>(R + (size_t)row * p.ldr + col);
+        *reinterpret_cast<f32x4_t*>(dst) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (col + e >= p.N) continue;
+          if constexpr (EPI == EPI_RESID) v[e] += R[(size_t)row * p.ldr + col + e];
+          dst[e] = v[e];
+        }
+      }
+    }
+    if constexpr (EPI == EPI_SWIGLU_COUNT) {
+#pragma unroll
+      for (int off = 1; off < 8; off <<= 1) cnt += __shfl_xor(cnt, off, kWave);
+      if ((threadIdx.x & 7) == 0 && cnt) atomicAdd(p.cnt + row, cnt);
+    }
+  }
+}
+
+template <int EPI>
+static void launch_gemm_f32_epi(const GemmParams& p, bool vec, hipStream_t s) {
+  // A 64x64 tile halves the operand loads per MFMA but leaves fewer, longer
+  // chains.  At 11,600 rows (d 512, 1448 such tiles) O and down take 148
+  // against 173 us with it and QKV 231 against 276; at 750 rows (288 tiles)
+  // 24 against 31 us without.  SwiGLU's two weights already share one set of
+  // activation loads: 399 us against 434 with the wide tile.  Element-wise
+  // loads cost four times the instructions, so there it pays earlier and for
+  // SwiGLU too (8400 rows, d_ff 687: 184 against 259 us).
+  const bool glu = EPI == EPI_SWIGLU || EPI == EPI_SWIGLU_COUNT;
+  const long long tiles = (long long)((p.N + 63) / 64) * ((p.m_ub + 63) / 64);
+  const bool wide = vec ? !glu && tiles >= 1024 : tiles >= 512;
+  const int tile = wide ? 64 : 32;
+  dim3 grid((p.N + tile - 1) / tile, (p.m_ub + tile - 1) / tile), block(256);
+  if (wide && vec) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 4, true>), grid, block, 0, s, p);
+  else if (wide) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 4, false>), grid, block, 0, s, p);
+  else if (vec) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, true>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, false>), grid, block, 0, s, p);
+}
+
+int launch_gemm_f32(int epi, const GemmParams& p, hipStream_t s) {
+  auto a16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+  const bool vec = p.K % 4 == 0 && p.N % 4 == 0 && p.lda % 4 == 0 && p.ldb % 4 == 0 && p.ldc % 4 == 0 &&
+                   p.ldr % 4 == 0 && a16(p.A) && a16(p.B) && a16(p.B2) && a16(p.C) && a16(p.R);
+  switch (epi) {
+    case EPI_SCALE: launch_gemm_f32_epi<EPI_SCALE>(p, vec, s); break;
+    case EPI_RESID: launch_gemm_f32_epi<EPI_RESID>(p, vec, s); break;
+    case EPI_SWIGLU: launch_gemm_f32_epi<EPI_SWIGLU>(p, vec, s); break;
+    case EPI_SWIGLU_COUNT: launch_gemm_f32_epi<EPI_SWIGLU_COUNT>(p, vec, s); break;
+    default: return -1;
+  }
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
 
 // ---------------------------------------------------------------------------
 // fp32 attention, one workgroup per (sequence, 16 queries, head).  The batches
