@@ -28,6 +28,9 @@ struct ArgmaxPartial {
   int pad;
 };
 
+// Tiles of a launch whose K can be split (fewer than the CUs / 2).
+constexpr int kSplitCounters = 256;
+
 // C[M,N] = A[M,K] * B[N,K]^T with a fused epilogue.  M is read on the device
 // from m_ptr (clamped to m_ub, the bound the grid is sized from).
 struct GemmParams {
@@ -68,15 +71,11 @@ struct GemmParams {
   // SEER_STATUS_V_RANGE (atomic OR) when a column stored as fp16 had a
   // magnitude above fp16's largest finite value
   int* status;
-  // bf16 SCALE, RESID_SPLIT, RESID_PAIR and SWIGLU, optional: scratch for
-  // fp32 partial tiles (partial_bytes bytes).  A launch whose 256x256 tiles
-  // fill at most a third of the n_units workgroups that run at once splits K
-  // over k_splits units per tile: each stores its fp32 partial sums, and a
-  // second kernel adds the splits in order and applies the epilogue.  The
-  // launcher sets k_splits; callers leave it 0.
+  // bf16, optional: scratch for the fp32 sums of launches of few tiles that
+  // split K (gemm_bf16_split_kernel: at most n_units x 64 KiB), and their
+  // arrival counters (kSplitCounters ints, zero at the launch; both or neither)
   float* partial;
-  size_t partial_bytes;
-  int k_splits;
+  int* counters;
   // bf16, optional: the 256-row tiles to compute.  mtiles[0] = their number,
   // mtiles[1 ..] = their indices t (rows 256 t .. 256 t + 255) in increasing
   // order, written on the device (launch_kept_tiles); the launch covers them
@@ -126,9 +125,11 @@ struct RopeArgs {
 };
 
 // inv_rms[r] = 1 / sqrt(mean_j x[r,j]^2 + eps) for r < M; with rope, also
-// the rotary positions and frequencies above.
+// the rotary positions and frequencies above.  zero, optional: zero_n ints to
+// clear on the way (the first workgroup).
 int launch_rms_inv(bool bf16, const void* x, int ld, int d, const int* m_ptr, int m_ub,
-                   float eps, float* out, hipStream_t s, const RopeArgs* rope = nullptr);
+                   float eps, float* out, hipStream_t s, const RopeArgs* rope = nullptr, int* zero = nullptr,
+                   int zero_n = 0);
 
 // fp32: rotate the q and k columns of qkv ([M, 3d]) in place with the
 // positions and frequencies written by launch_rms_inv.

@@ -10,7 +10,8 @@ namespace seer {
 // GEMM: (x * inv_rms) W^T = inv_rms * (x W^T).
 template <bool BF16>
 __global__ __launch_bounds__(256) void rms_inv_kernel(const void* x, int ld, int d, const int* m_ptr,
-                                                      int m_ub, float eps, float* out, RopeArgs rope) {
+                                                      int m_ub, float eps, float* out, RopeArgs rope, int* zero,
+                                                      int zero_n) {
   const int M = rows_from(m_ptr, m_ub);
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
@@ -18,6 +19,8 @@ __global__ __launch_bounds__(256) void rms_inv_kernel(const void* x, int ld, int
     const int j = threadIdx.x;
     rope.freq[j] = pow((double)rope.theta, -2.0 * j / rope.head_dim) / 6.283185307179586;   // / (2 pi)
   }
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < zero_n; i += 256) zero[i] = 0;
   if (row >= M) return;
   if (rope.pos && lane == 0) {
     // sequence of the row: the last b with cu[b] <= row
@@ -64,14 +67,14 @@ __global__ __launch_bounds__(256) void rms_inv_kernel(const void* x, int ld, int
 }
 
 int launch_rms_inv(bool bf16, const void* x, int ld, int d, const int* m_ptr, int m_ub, float eps,
-                   float* out, hipStream_t s, const RopeArgs* rope) {
+                   float* out, hipStream_t s, const RopeArgs* rope, int* zero, int zero_n) {
   dim3 grid((m_ub + 3) / 4), block(256);
   RopeArgs r{};
   if (rope) r = *rope;
   if (bf16)
-    hipLaunchKernelGGL(rms_inv_kernel<true>, grid, block, 0, s, x, ld, d, m_ptr, m_ub, eps, out, r);
+    hipLaunchKernelGGL(rms_inv_kernel<true>, grid, block, 0, s, x, ld, d, m_ptr, m_ub, eps, out, r, zero, zero_n);
   else
-    hipLaunchKernelGGL(rms_inv_kernel<false>, grid, block, 0, s, x, ld, d, m_ptr, m_ub, eps, out, r);
+    hipLaunchKernelGGL(rms_inv_kernel<false>, grid, block, 0, s, x, ld, d, m_ptr, m_ub, eps, out, r, zero, zero_n);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -69,10 +69,11 @@ struct WsLayout {
   size_t qkv, o, h1, act, inv1, inv2, h1lo, pos, freq, tmap, part, part_bytes, total;
 };
 
-// bf16 layers: fp32 partial tiles of the GEMMs that split K (launches whose
-// tiles fill at most half of the CUs; at most one 256x256 fp32 tile per
-// workgroup of one round, 256 CUs x 256 KiB).
+// bf16 layers: fp32 sums of the GEMMs that split K (launches of few tiles; at
+// most 64 KiB per workgroup of one round of 256 CUs), and at the region's end
+// the arrival counters of the layer's four GEMMs.
 constexpr size_t PART_BYTES = (size_t)64 << 20;
+constexpr size_t COUNTER_BYTES = 4 * seer::kSplitCounters * sizeof(int);
 
 // The first 256 bytes of a layer workspace are a header whose first int32 is
 // the status word (same place for every rows bound, so it persists across
@@ -229,6 +230,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
   int* rpos = reinterpret_cast<int*>(ws + L.pos);
   double* rfreq = reinterpret_cast<double*>(ws + L.freq);
   float* part = L.part_bytes ? reinterpret_cast<float*>(ws + L.part) : nullptr;
+  int* counters = L.part_bytes ? reinterpret_cast<int*>(ws + L.part + L.part_bytes - COUNTER_BYTES) : nullptr;
   int n_units = 0;                      // CUs: sizes the split of a partly filled last GEMM round
   if (bf16) {
     int dev = 0;
@@ -252,7 +254,8 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
     seer::RopeArgs ra{};
     ra.cu = cu_seqlens; ra.B = batch; ra.cu_kv = cu_kv; ra.pos = rpos; ra.freq = rfreq;
     ra.theta = dims->rope_theta; ra.head_dim = dims->head_dim;
-    if (seer::launch_rms_inv(bf16, x_in, d, d, m_ptr, R, dims->rms_eps, inv1, stream, rope ? &ra : nullptr))
+    if (seer::launch_rms_inv(bf16, x_in, d, d, m_ptr, R, dims->rms_eps, inv1, stream, rope ? &ra : nullptr,
+                             counters, counters ? 4 * seer::kSplitCounters : 0))
       return hip_fail("rms launch");
   }
   // 2. QKV projection, RMSNorm folded in as a row scale
@@ -260,7 +263,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
   {
     seer::GemmParams g{};
     g.n_units = n_units;
-    g.partial = part; g.partial_bytes = L.part_bytes;
+    g.partial = part; g.counters = counters;
     g.A = x_in; g.B = wb + P.qkv * es; g.C = qkv; g.rs = inv1;
     g.m_ptr = m_ptr; g.m_ub = R; g.N = 3 * d; g.K = d;
     g.lda = d; g.ldb = d; g.ldc = 3 * d;
@@ -295,7 +298,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
   {
     seer::GemmParams g{};
     g.n_units = n_units;
-    g.partial = part; g.partial_bytes = L.part_bytes;
+    g.partial = part; g.counters = counters + seer::kSplitCounters;
     g.A = o; g.B = wb + P.o * es; g.C = h1; g.R = x_in; g.C2 = h1lo;
     g.m_ptr = m_ptr; g.m_ub = R; g.N = d; g.K = d;
     g.lda = d; g.ldb = d; g.ldc = d; g.ldr = d;
@@ -310,7 +313,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
     if (act_count && seer::launch_zero_i32(act_count, R, stream)) return hip_fail("zero launch");
     seer::GemmParams g{};
     g.n_units = n_units;
-    g.partial = part; g.partial_bytes = L.part_bytes;
+    g.partial = part; g.counters = counters + 2 * seer::kSplitCounters;
     g.A = h1; g.C = act; g.rs = inv2; g.cnt = act_count; g.eps = act_eps;
     g.m_ptr = m_ptr; g.m_ub = R; g.K = d; g.lda = d; g.ldb = d; g.ldc = I;
     if (bf16) {
@@ -352,7 +355,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
   {
     seer::GemmParams g{};
     g.n_units = n_units;
-    g.partial = part; g.partial_bytes = L.part_bytes;
+    g.partial = part; g.counters = counters + 3 * seer::kSplitCounters;
     g.A = act; g.B = wb + P.dn * es; g.C = x_out; g.R = h1; g.R2 = h1lo;
     g.m_ptr = m_ptr; g.m_ub = R; g.N = d; g.K = I;
     g.lda = I; g.ldb = I; g.ldc = d; g.ldr = d;
