@@ -352,13 +352,271 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_kernel(AttnParams p) {
   }
 }
 
+// Few query tiles (one cached request, a small model): the kernel above would
+// leave most CUs idle while each of its workgroups walks every key in turn.
+// Here a workgroup takes 32 queries of one head and its four waves a quarter
+// of the keys each (32 of every 128), with K and V tiles of the wave's own, so
+// the loop has no barrier; the four partial results are merged through LDS.
+// What bounds it is the latency of that walk: one tile's loads are in flight
+// while the tile before is multiplied.  One cached request (97 rows, 890 keys,
+// 32 heads) takes 174 -> 163 us in all.
+constexpr int QF = 32;                  // queries per workgroup
+constexpr int KF = 32;                  // keys per wave and tile
+constexpr int FT = KF * K_ROW;          // bytes of one wave's K or V tile
+
+__global__ __launch_bounds__(NT, 1) void attn_few_bf16_kernel(AttnParams p) {
+  __shared__ __attribute__((aligned(1024))) uint8_t k_lds0[4 * FT];
+  __shared__ __attribute__((aligned(1024))) uint8_t k_lds1[4 * FT];
+  __shared__ __attribute__((aligned(1024))) uint8_t v_lds0[4 * FT];
+  __shared__ __attribute__((aligned(1024))) uint8_t v_lds1[4 * FT];
+  __shared__ float m_first[QF], m_part[4][QF], l_part[4][QF];
+
+  // one XCD takes the query tiles of a head together, which share K and V
+  const int gx = gridDim.x;
+  const int unit = xcd_remap(blockIdx.x + gx * blockIdx.y, gx * gridDim.y);
+  const int h = unit / gx;
+  int b, t;
+  if (!tile_of(p.cu, p.B, QF, unit % gx, b, t)) return;
+  b = __builtin_amdgcn_readfirstlane(b);
+  t = __builtin_amdgcn_readfirstlane(t);
+  const int s0 = p.cu[b];
+  if (s0 < 0 || s0 >= p.rows_ub) return;
+  int len = p.cu[b + 1] - s0;
+  len = len > p.rows_ub - s0 ? p.rows_ub - s0 : len;   // never touch rows past the bound
+  if (t * QF >= len) return;
+  int used = p.used ? p.used[b] : len;
+  used = used < 0 ? 0 : (used > len ? len : used);
+  int P = 0, kv0 = 0;
+  if (p.cu_kv) {
+    kv0 = p.cu_kv[b];
+    P = p.cu_kv[b + 1] - kv0;
+    P = P < 0 ? 0 : P;
+  }
+  // key positions as above: cache rows, a gap up to a multiple of 4, own rows
+  const int P4 = (P + 3) & ~3;
+  const int nk = used > 0 ? P4 + used : P;
+
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int fr = lane & 31;
+  const int fhalf = lane >> 5;
+  const uint32_t ld = 3u * (uint32_t)p.d;
+  const uint16_t* seq = static_cast<const uint16_t*>(p.qkv) + (size_t)s0 * ld;
+  const int q_row = t * QF + fr;
+  const int q_src = q_row < len ? q_row : len - 1;
+  bf16x8_t qf[8];
+  {
+    const uint16_t* qp = seq + (uint32_t)q_src * ld + h * DH + fhalf * 8;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(qp + ks * 16));
+  }
+  f32x16_t o[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[i][r] = 0.0f;
+  float m_run = -INFINITY;
+  float l_run = 0.0f;
+  const float c = p.scale * 1.4426950408889634f;
+
+  // staging as above, a tile's 32 rows by the wave that reads them
+  const __amdgpu_buffer_rsrc_t rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(seq), 0, -1, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs_c = __builtin_amdgcn_make_buffer_rsrc(
+      p.cu_kv ? const_cast<uint16_t*>(static_cast<const uint16_t*>(p.kv) + (size_t)kv0 * 2 * p.d)
+              : const_cast<uint16_t*>(seq), 0, -1, 0x00020000);
+  const uint32_t q_row_bytes = 3u * (uint32_t)p.d * 2u, c_row_bytes = 4u * (uint32_t)p.d;
+  const uint32_t k_col = (uint32_t)(p.d + h * DH) * 2u, c_col = (uint32_t)(h * DH) * 2u, v_step = (uint32_t)p.d * 2u;
+  auto dma_tile = [&](int kbase, auto buf_tag) {
+    constexpr int B_ = decltype(buf_tag)::value;
+    uint8_t* kb = (B_ ? k_lds1 : k_lds0) + wv * FT;
+    uint8_t* vb = (B_ ? v_lds1 : v_lds0) + wv * FT;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int r = 4 * q + (lane >> 4);
+      int key = kbase + r;
+      key = key < nk ? key : nk - 1;
+      const uint32_t ck = (uint32_t)(((lane & 15) ^ (r & 15)) << 4);
+      const uint32_t cv = (uint32_t)(((lane & 15) ^ (4 * (r & 3))) << 4);
+      const bool cache = kbase + 4 * q < P4 || used == 0;
+      // a load wholly past the keys re-reads the last one, wherever it lies
+      const int row = cache ? (key < P ? key : P - 1) : key - P4;
+      const uint32_t ro = (uint32_t)row * (cache ? c_row_bytes : q_row_bytes) + (cache ? c_col : k_col);
+      const __amdgpu_buffer_rsrc_t rs = cache ? rs_c : rs_q;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(kb + 4 * q * K_ROW), 16, ro + ck, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(vb + 4 * q * K_ROW), 16, ro + v_step + cv, 0, 0, 0);
+    }
+  };
+
+  // tiles of this wave: keys 32 wv, 32 wv + 128, ...; each holds at least one key
+  const int n = nk > KF * wv ? (nk - KF * wv + 4 * KF - 1) / (4 * KF) : 0;
+  if (n > 0) dma_tile(KF * wv, std::integral_constant<int, 0>{});
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0)
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  // waits for the wave's LDS accesses only: the loads of tile 1 stay in flight
+  auto first_barrier = [&]() {
+    __builtin_amdgcn_s_waitcnt(0xc07f);     // lgkmcnt(0)
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (n == 0) first_barrier();              // a wave without keys: the others' barrier
+  auto tile_step = [&](int kt, auto buf_tag) {
+    constexpr int BUF = decltype(buf_tag)::value;
+    const int kbase = KF * (wv + 4 * kt);
+    const uint8_t* kl = (BUF ? k_lds1 : k_lds0) + wv * FT;
+    const uint8_t* vl = (BUF ? v_lds1 : v_lds0) + wv * FT;
+    if (kt + 1 < n) dma_tile(kbase + 4 * KF, std::integral_constant<int, BUF ^ 1>{});
+    f32x16_t s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.0f;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const int ch = (2 * ks + fhalf) ^ (fr & 15);
+      const bf16x8_t kf = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(kl + fr * K_ROW + ch * 16));
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], s, 0, 0, 0);
+    }
+    if (kbase + KF > nk || (P < P4 && kbase < P4 && kbase + KF > P)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int key = kbase + (r >> 2) * 8 + fhalf * 4 + (r & 3);
+        if (key >= nk || (key >= P && key < P4)) s[r] = -INFINITY;
+      }
+    }
+    // probabilities as above
+    f16x8_t pf[2];
+    float lsum;
+    auto probs = [&]() {
+      const float mc = m_run * c;
+      const f16x2_t one2 = {(_Float16)1.0f, (_Float16)1.0f};
+      lsum = 0.0f;
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl) {
+        u32x4_t pk;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float p0 = __builtin_amdgcn_exp2f(s[sl * 8 + 2 * e] * c - mc);
+          const float p1 = __builtin_amdgcn_exp2f(s[sl * 8 + 2 * e + 1] * c - mc);
+          const f16x2_t hp = __builtin_convertvector(f32x2_t{p0, p1}, f16x2_t);
+          lsum = __builtin_amdgcn_fdot2(hp, one2, lsum, false);
+          pk[e] = __builtin_bit_cast(uint32_t, hp);
+        }
+        pf[sl] = __builtin_bit_cast(f16x8_t, pk);
+      }
+    };
+    auto tile_max = [&]() {
+      float mt = s[0];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mt = fmaxf(mt, s[r]);
+      const u32x2_t sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
+      return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    };
+    // The maximum of the first 32 keys is every wave's first reference, so
+    // that a probability is rounded alike whichever wave its key falls to.
+    if (kt == 0) {
+      if (wv == 0) {
+        m_run = tile_max();
+        if (fhalf == 0) m_first[fr] = m_run;
+      }
+      first_barrier();
+      m_run = m_first[fr];
+    }
+    probs();
+    if (__any(!(lsum < INFINITY))) {
+      const float m_new = fmaxf(m_run, tile_max());
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c);
+      m_run = m_new;
+      l_run *= alpha;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[i][r] *= alpha;
+      probs();
+    }
+    l_run += lsum;
+    // O^T += V^T P^T: fragments by the transpose read, as above
+    const int il = lane & 15;
+    const int vkey = 4 * fhalf + (il >> 2);
+    const int vc8 = 4 * ((lane >> 4) & 1) + (il & 3);
+#pragma unroll
+    for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) {
+        const int c8 = (8 * dt + vc8) ^ (8 * (vkey & 3));
+        const uint8_t* a = vl + (vkey + 16 * sl) * K_ROW + (c8 << 3);
+        const v4i16_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)a);
+        const v4i16_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t*)(a + 8 * K_ROW));
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+            __builtin_bit_cast(f16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7)), pf[sl], o[dt], 0, 0, 0);
+      }
+    // the next tile has landed; this one's fragments were consumed above, so
+    // the step after may overwrite it
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0070);     // vmcnt(0) and lgkmcnt(0)
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int kt = 0; kt < n; kt += 2) {
+    tile_step(kt, std::integral_constant<int, 0>{});
+    if (kt + 1 < n) tile_step(kt + 1, std::integral_constant<int, 1>{});
+  }
+
+  // ---- merge: each wave leaves O in its own K tiles, then ends with 32 dims ----
+  const float l_own = l_run + __shfl_xor(l_run, 32, kWave);
+  if (fhalf == 0) {
+    m_part[wv][fr] = m_run;
+    l_part[wv][fr] = l_own;
+  }
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<f32x4_t*>((dt & 2 ? k_lds1 : k_lds0) + wv * FT + ((dt & 1) * 4 + g) * 1024 + lane * 16) =
+          f32x4_t{o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
+  __syncthreads();
+  if (q_row >= len) return;
+  // waves without keys (the last ones of fewer than 97) weigh nothing
+  const int live = nk > 3 * KF ? 4 : (nk + KF - 1) / KF;
+  float m = -INFINITY;
+  for (int v = 0; v < live; ++v) m = fmaxf(m, m_part[v][fr]);
+  float l_tot = 0.0f;
+  f32x4_t sum[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) sum[g] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int v = 0; v < live; ++v) {
+    const float w = __builtin_amdgcn_exp2f((m_part[v][fr] - m) * c);
+    l_tot += l_part[v][fr] * w;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      sum[g] += w * *reinterpret_cast<const f32x4_t*>((wv & 2 ? k_lds1 : k_lds0) + v * FT + ((wv & 1) * 4 + g) * 1024 + lane * 16);
+  }
+  const float inv = (q_row < used && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
+  uint16_t* op = static_cast<uint16_t*>(p.out) + (size_t)(s0 + q_row) * p.d + h * DH + wv * 32 + fhalf * 4;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    uint2 v;
+    v.x = pack_bf2(sum[g][0] * inv, sum[g][1] * inv);
+    v.y = pack_bf2(sum[g][2] * inv, sum[g][3] * inv);
+    *reinterpret_cast<uint2*>(op + g * 8) = v;
+  }
+}
+
 int launch_attn_bf16(const AttnParams& p, hipStream_t s) {
   if (p.head_dim != DH) return -1;
   // byte offsets inside the qkv rows and the cache rows are 32-bit
   if ((uint64_t)p.rows_ub * 3u * (uint64_t)p.d * 2u >= (1ull << 32)) return -1;
   if (p.cu_kv && !p.kv) return -1;
-  dim3 grid((p.rows_ub + QT - 1) / QT + p.B, p.n_heads), block(NT);
-  hipLaunchKernelGGL(attn_bf16_kernel, grid, block, 0, s, p);
+  const dim3 block(NT);
+  // up to half a round of the 256 CUs (measured at 64 tiles, 174 -> 163 us, and
+  // 40, 312 -> 305 us); past a round the split walks only add K and V loads
+  constexpr int kFewTiles = 128;
+  if ((p.rows_ub + QT - 1) / QT * p.n_heads <= kFewTiles) {
+    const dim3 grid((p.rows_ub + QF - 1) / QF + p.B, p.n_heads);
+    hipLaunchKernelGGL(attn_few_bf16_kernel, grid, block, 0, s, p);
+  } else {
+    const dim3 grid((p.rows_ub + QT - 1) / QT + p.B, p.n_heads);
+    hipLaunchKernelGGL(attn_bf16_kernel, grid, block, 0, s, p);
+  }
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -1,0 +1,97 @@
+"""Attention of few query tiles (32 queries a workgroup, the keys split over its
+waves) and the form that larger bounds take, over the same sequences: the output
+that a layer call leaves in its workspace against float64 attention of the q, k
+and v that it left there.  Lengths around the 32-query tiles and the 32 keys of
+a wave, padding rows, sequences without keys, cached prefixes whose end is no
+multiple of 4, and scores that rise past the fp16 range of the first tile's
+reference maximum."""
+import numpy as np
+import pytest
+
+from gpu_util import dev, log, view_ws
+
+pytestmark = pytest.mark.gpu
+
+LENS = [1, 31, 32, 33, 64, 65, 97, 128, 129, 300, 40]
+FORMS = {
+    # heads, lengths, used (None: all), cached prefixes (None: no cache), factor of the later keys
+    "own": (2, LENS, None, None, 1.0),
+    "padded": (2, LENS, [0, 1, 32, 30, 33, 64, 96, 127, 128, 200, 0], None, 1.0),
+    "prefix": (2, LENS, None, [0, 1, 2, 3, 31, 32, 33, 95, 127, 130, 401], 1.0),
+    "prefix_padded": (2, LENS, [0, 1, 32, 30, 33, 64, 96, 127, 128, 200, 0], [5, 0, 97, 3, 31, 64, 1, 128, 6, 401, 0], 1.0),
+    "rising": (1, [700], None, None, 40.0),
+    "one_row": (4, [1], None, [793], 1.0),
+}
+
+
+@pytest.fixture(scope="module")
+def S():
+    from paper_2607_14557_amd import seer
+    seer.load_library()
+    return seer
+
+
+@pytest.mark.parametrize("bound", ["few", "many"])
+@pytest.mark.parametrize("name", list(FORMS))
+def test_attention_forms(S, name, bound):
+    import torch
+    from paper_2607_14557_amd.runner import SeerStack, dims_for
+    H, lens, used, prefix, factor = FORMS[name]
+    d, T, B = 128 * H, sum(lens), len(lens)
+    d, I = max(d, 256), 256
+    H = d // 128
+    ub = T + 7 if bound == "few" else 128 * 128 // H + 128 + T
+    assert (-(-ub // 128) * H <= 128) == (bound == "few")
+    log("attention %s, %s tiles: %d heads, %d rows, bound %d" % (name, bound, H, T, ub))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    f = lambda *s: (torch.randn(*s, device="cuda", generator=gen) * 0.06).bfloat16()
+    W = dict(wq=f(d, d), wk=f(d, d), wv=f(d, d), wo=f(d, d), wg=f(I, d), wu=f(I, d), wd=f(d, I),
+             g1=torch.ones(d, device="cuda"), g2=torch.ones(d, device="cuda"))
+    if factor != 1.0:
+        W["wk"] = (W["wq"].float() * 0.3).bfloat16()   # scores that grow with the rows' likeness
+    st = SeerStack(dims_for(d, H, 128, I, "bf16"), 1, ub)
+    st.set_layer(0, W)
+    x = torch.randn(ub, d, device="cuda", generator=gen).bfloat16()
+    if factor != 1.0:
+        x[T // 2:T] = (x[:1].float() + 0.2 * x[T // 2:T].float()).bfloat16()
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    un = np.array(used if used else lens)
+    y = torch.empty_like(x)
+    cu_kv = np.concatenate([[0], np.cumsum(prefix)]) if prefix else None
+    if prefix:
+        n = int(cu_kv[-1])
+        kv = torch.cat([f(n, d) * 16, (f(n, d) * 16).to(torch.float16).view(torch.bfloat16)], dim=1).contiguous()
+        S.seer_layer_forward_cached(st.dims, st.packed[0], x, y, ub, dev(cu), dev(un), B, kv, dev(cu_kv), n,
+                                    st.workspace)
+    else:
+        st.layer(0, x, y, dev(cu), dev(un), B, ub)
+    torch.cuda.synchronize()
+    off = S.seer_layer_workspace_offsets(st.dims, ub)
+    qkv = view_ws(st.workspace, off[0], ub, 3 * d, "bf16")[:T].contiguous()
+    o = view_ws(st.workspace, off[1], ub, d, "bf16")[:T].double()
+    q, k, v = qkv[:, :d].double(), qkv[:, d:2 * d].double(), qkv.view(torch.float16)[:, 2 * d:].double()
+    worst = 0.0
+    for b in range(B):
+        r, u = slice(int(cu[b]), int(cu[b + 1])), slice(int(cu[b]), int(cu[b]) + int(un[b]))
+        assert bool((o[u.stop:r.stop] == 0).all()), "padding rows of sequence %d" % b
+        if un[b] == 0:
+            continue
+        kb, vb = k[u], v[u]
+        if prefix:
+            c = slice(int(cu_kv[b]), int(cu_kv[b + 1]))
+            kb = torch.cat([kv[c, :d].double(), kb])
+            vb = torch.cat([kv.view(torch.float16)[c, d:].double(), vb])
+        for h in range(H):
+            s = slice(128 * h, 128 * h + 128)
+            z = q[u, s] @ kb[:, s].t().contiguous() / 128 ** 0.5
+            pr = torch.softmax(z, dim=1)
+            ref, mag = pr @ vb[:, s].contiguous(), pr @ vb[:, s].abs().contiguous()
+            # half an ulp of the bf16 output; an fp16 rounding of each probability and of their sum (2^-11 each,
+            # and 2^-25 a key for those below fp16's normal range); fp32 scores of 128 terms in the exponent
+            zmag = (q[u, s].abs() @ kb[:, s].abs().t().contiguous()).amax(dim=1, keepdim=True) / 128 ** 0.5
+            tol = 2.0 ** -8 * ref.abs() + mag * (2.0 ** -10 + 8 * zmag * 2.0 ** -24) \
+                + kb.shape[0] * 2.0 ** -25 * vb[:, s].abs().amax() + 1e-30
+            worst = max(worst, ((o[u, s] - ref).abs() / tol).max().item())
+    log("  largest error over its bound: %.2f" % worst)
+    assert worst <= 1.0
