@@ -359,7 +359,7 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_kernel(AttnParams p) {
 // the loop has no barrier; the four partial results are merged through LDS.
 // What bounds it is the latency of that walk: one tile's loads are in flight
 // while the tile before is multiplied.  One cached request (97 rows, 890 keys,
-// 32 heads) takes 174 -> 163 us in all.
+// 32 heads) takes 174 -> 165 us in all.
 constexpr int QF = 32;                  // queries per workgroup
 constexpr int KF = 32;                  // keys per wave and tile
 constexpr int FT = KF * K_ROW;          // bytes of one wave's K or V tile
@@ -607,7 +607,7 @@ int launch_attn_bf16(const AttnParams& p, hipStream_t s) {
   if ((uint64_t)p.rows_ub * 3u * (uint64_t)p.d * 2u >= (1ull << 32)) return -1;
   if (p.cu_kv && !p.kv) return -1;
   const dim3 block(NT);
-  // up to half a round of the 256 CUs (measured at 64 tiles, 174 -> 163 us, and
+  // up to half a round of the 256 CUs (measured at 64 tiles, 174 -> 165 us, and
   // 40, 312 -> 305 us); past a round the split walks only add K and V loads
   constexpr int kFewTiles = 128;
   if ((p.rows_ub + QT - 1) / QT * p.n_heads <= kFewTiles) {
