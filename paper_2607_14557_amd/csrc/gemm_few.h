@@ -295,8 +295,8 @@ __device__ __forceinline__ void few_tile(const GemmParams& p, uint8_t* st0, uint
   // on goes to stage SF (whose fragments were consumed in the step before) and
   // half the slices of tile T + 1 to the other set.  Before the
   // look-ahead read of the next half (stage SN, loaded two steps ago) its
-  // loads must have landed: those of the last step and three quarters of this
-  // one's may be in flight.
+  // loads must have landed: what was issued since, the last step's A and half
+  // set of B and this one's but its last quarter of A, may be in flight.
 #define FEW_STEP(T, H, SC, SN, SF, BS)                                                                            \
   {                                                                                                               \
     _Pragma("unroll") for (int ks = 0; ks < 4; ++ks) {                                                            \
@@ -315,9 +315,14 @@ __device__ __forceinline__ void few_tile(const GemmParams& p, uint8_t* st0, uint
     }                                                                                                             \
   }
 
+  // in the steps' order, so that their wait covers the first one too: younger
+  // than st1's loads are half a set of B, st2's and the first step's
   _Pragma("unroll") for (int q = 0; q < 4; ++q) FEW_A(st0, 0, 0, q);
-  _Pragma("unroll") for (int q = 0; q < 4; ++q) FEW_B(0, 0, q);
+  _Pragma("unroll") for (int q = 0; q < 2; ++q) FEW_B(0, 0, q);
+  __builtin_amdgcn_sched_barrier(0);
   _Pragma("unroll") for (int q = 0; q < 4; ++q) FEW_A(st1, 0, 1, q);
+  __builtin_amdgcn_sched_barrier(0);
+  _Pragma("unroll") for (int q = 2; q < 4; ++q) FEW_B(0, 0, q);
   _Pragma("unroll") for (int q = 0; q < 4; ++q) FEW_A(st2, 1, 0, q);
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(16 + 4 * NJ, 15));
