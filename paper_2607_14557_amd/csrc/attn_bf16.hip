@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "dispatch.h"
 #include "kernels.h"
 
 namespace seer {
@@ -358,9 +359,10 @@ __global__ __launch_bounds__(NT, 2) void attn_bf16_kernel(AttnParams p) {
 // of the keys each (32 of every 128), with K and V tiles of the wave's own, so
 // the loop has no barrier; the four partial results are merged through LDS.
 // What bounds it is the latency of that walk: one tile's loads are in flight
-// while the tile before is multiplied.  One cached request (97 rows, 890 keys,
-// 32 heads) takes 174 -> 165 us in all.
-constexpr int QF = 32;                  // queries per workgroup
+// while the tile before is multiplied.  One cached request of 128 rows and 800
+// cached keys, 32 heads: 23.5 -> 15.4 us; with 3700 cached keys and 256 rows
+// 77 -> 50.  few_attention has where it pays.
+constexpr int QF = kFewQueries;         // queries per workgroup
 constexpr int KF = 32;                  // keys per wave and tile
 constexpr int FT = KF * K_ROW;          // bytes of one wave's K or V tile
 
@@ -607,11 +609,12 @@ int launch_attn_bf16(const AttnParams& p, hipStream_t s) {
   if ((uint64_t)p.rows_ub * 3u * (uint64_t)p.d * 2u >= (1ull << 32)) return -1;
   if (p.cu_kv && !p.kv) return -1;
   const dim3 block(NT);
-  // up to half a round of the 256 CUs (measured at 64 tiles, 174 -> 165 us, and
-  // 40, 312 -> 305 us); past a round the split walks only add K and V loads
-  constexpr int kFewTiles = 128;
-  if ((p.rows_ub + QT - 1) / QT * p.n_heads <= kFewTiles) {
-    const dim3 grid((p.rows_ub + QF - 1) / QF + p.B, p.n_heads);
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return -1;
+  if (few_attention(p.rows_ub, p.B, p.n_heads, p.kv_rows_ub, cus)) {
+    const dim3 grid(max_row_tiles(p.rows_ub, p.B, QF), p.n_heads);
     hipLaunchKernelGGL(attn_few_bf16_kernel, grid, block, 0, s, p);
   } else {
     const dim3 grid((p.rows_ub + QT - 1) / QT + p.B, p.n_heads);

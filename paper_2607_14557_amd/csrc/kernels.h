@@ -152,6 +152,7 @@ struct AttnParams {
   // types of the K and V thirds of qkv), ahead of its own keys; null: none
   const void* kv;
   const int* cu_kv;
+  int kv_rows_ub;        // bound on cu_kv[B] (0 without a cache)
 };
 
 int launch_attn_bf16(const AttnParams& p, hipStream_t s);

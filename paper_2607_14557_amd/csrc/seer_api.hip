@@ -191,7 +191,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
                               const int32_t* seqused, int32_t batch, float act_eps,
                               int32_t* act_count, void* workspace, size_t workspace_bytes,
                               hipStream_t stream, hipEvent_t* ev, const void* kv_cache = nullptr,
-                              const int32_t* cu_kv = nullptr, bool own_status = false,
+                              const int32_t* cu_kv = nullptr, int32_t kv_rows_ub = 0, bool own_status = false,
                               int32_t* status = nullptr, const DetectStep* det = nullptr) {
   int rc = check_dims(dims);
   if (rc) return rc;
@@ -289,7 +289,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
     a.qkv = qkv; a.out = o; a.cu = cu_seqlens; a.used = seqused; a.B = batch;
     a.d = d; a.n_heads = dims->n_heads; a.head_dim = dims->head_dim; a.rows_ub = R;
     a.scale = 1.0f / sqrtf((float)dims->head_dim);
-    a.kv = kv_cache; a.cu_kv = cu_kv;
+    a.kv = kv_cache; a.cu_kv = cu_kv; a.kv_rows_ub = kv_rows_ub;
     if ((bf16 ? seer::launch_attn_bf16(a, stream) : seer::launch_attn_f32(a, stream)))
       return hip_fail("attention launch");
   }
@@ -377,7 +377,7 @@ static int layer_detect_impl(const seer_dims* dims, const void* w_packed, const 
   if (rc) return rc;
   const DetectStep det{win_off, win_len, params, boundary, keep_len};
   return layer_forward_impl(dims, w_packed, x_in, x_out, total_rows_ub, cu_seqlens, nullptr, batch, act_eps,
-                            act_count, workspace, workspace_bytes, stream, ev, nullptr, nullptr, false, nullptr,
+                            act_count, workspace, workspace_bytes, stream, ev, nullptr, nullptr, 0, false, nullptr,
                             &det);
 }
 
@@ -462,7 +462,7 @@ int seer_layer_forward_varlen_noalloc(const seer_dims* dims, const void* w_packe
   rc = scratch_of_current_device(&ws);
   if (rc) return rc;
   return layer_forward_impl(dims, w_packed, x_in, x_out, total_rows_ub, cu_seqlens, seqused, batch, act_eps,
-                            act_count, ws, kScratchBytes, stream, nullptr, nullptr, nullptr, true, status);
+                            act_count, ws, kScratchBytes, stream, nullptr, nullptr, nullptr, 0, true, status);
 }
 
 int seer_layer_forward_varlen_timed(const seer_dims* dims, const void* w_packed, const void* x_in,
@@ -488,7 +488,7 @@ int seer_layer_forward_cached(const seer_dims* dims, const void* w_packed, const
   if ((size_t)kv_rows_ub * 2 * (size_t)dims->d_model >= ((size_t)1 << 32))
     return fail(SEER_EUNSUPPORTED, "kv_rows_ub %d is too large: cache element offsets must fit 32 bits", kv_rows_ub);
   return layer_forward_impl(dims, w_packed, x_in, x_out, total_rows_ub, cu_seqlens, seqused, batch, 0.0f,
-                            nullptr, workspace, workspace_bytes, stream, nullptr, kv_cache, cu_kv);
+                            nullptr, workspace, workspace_bytes, stream, nullptr, kv_cache, cu_kv, kv_rows_ub);
 }
 
 int seer_kv_export(const seer_dims* dims, const void* workspace, size_t workspace_bytes,

@@ -40,8 +40,9 @@ def test_attention_forms(S, name, bound):
     d, T, B = 128 * H, sum(lens), len(lens)
     d, I = max(d, 256), 256
     H = d // 128
-    ub = T + 7 if bound == "few" else 128 * 128 // H + 128 + T
-    assert (-(-ub // 128) * H <= 128) == (bound == "few")
+    # the rule sees the bounds: one round of 32-query tiles and 320 keys a sequence, or several rounds
+    ub = max(T + 7, 320 * B) if bound == "few" else 128 * 128 // H + 128 + T
+    assert (((ub - B) // 32 + B) * H <= 256) == (bound == "few")
     log("attention %s, %s tiles: %d heads, %d rows, bound %d" % (name, bound, H, T, ub))
     gen = torch.Generator(device="cuda")
     gen.manual_seed(5)
