@@ -45,6 +45,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "dispatch.h"
 #include "kernels.h"
 
 namespace seer {
@@ -108,12 +109,13 @@ __device__ __forceinline__ void seer_slice_schedule() {
   __builtin_amdgcn_sched_group_barrier(0x008, NM - NR / 2 - NV, 0);
 }
 
-// One BMTx256 output tile over KT K tiles of 64.  BMT = 256 is
+// One BMTx256 output tile over K tiles [kt0, kt0 + KT) of 64.  BMT = 256 is
 // the main tile; BMT = 128 serves the halves of the tiles of a partly filled
-// last round.  Wave w owns columns n0 + 64 w .. +63 and all BMT rows.
-template <int EPI, int BMT>
+// last round.  Wave w owns columns n0 + 64 w .. +63 and all BMT rows.  PART:
+// the tile's fp32 sums go to `sums` instead of through the epilogue.
+template <int EPI, int BMT, bool PART = false>
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint8_t* st0, uint8_t* st1, uint8_t* st2, uint8_t* st3,
-                                          int M, int m0, int n0, int KT) {
+                                          int M, int m0, int n0, int KT, int kt0 = 0, float* sums = nullptr) {
   constexpr int NI = BMT / 32;                      // 32-row MFMA tiles per wave
   constexpr int NA = BMT / 32;                      // A loads (1 KiB each) per wave and K tile
   constexpr int AP = NA / 4;                        // ... per slice
@@ -146,7 +148,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint8_t* st0, uin
   // quarter q (instructions AP q .. AP q + AP - 1) of A tile t into stage stg
   auto dma_a = [&](uint8_t* stg, int t, int q) {
     const int t_ = t < KT ? t : KT - 1;
-    const uint32_t ko = (uint32_t)t_ * (BK * 2);
+    const uint32_t ko = (uint32_t)(kt0 + t_) * (BK * 2);
 #pragma unroll
     for (int i = AP * q; i < AP * q + AP; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsa, (lds_void_t*)(stg + 8 * (NA * wv + i) * ROW_BYTES), 16, a_src[i],
@@ -162,7 +164,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint8_t* st0, uin
   // fill (rows of 128 bytes, the swizzle of A), so its epilogue reads them
   // after its own vmcnt wait, with no barrier.  Per quarter the same number of
   // loads as dma_a, so the ring's wait counts hold.
-  constexpr bool kResLds = (EPI == EPI_RESID_SPLIT || EPI == EPI_RESID_PAIR) && BMT == 256;
+  constexpr bool kResLds = (EPI == EPI_RESID_SPLIT || EPI == EPI_RESID_PAIR) && BMT == 256 && !PART;
   const bool res_lds = kResLds && KT >= 4 && (KT & 3) == 0;
   // For the residual pair (R high, R2 low) the three parts are R rows 0..63,
   // R2 rows 0..63 and R rows 64..127.
@@ -219,7 +221,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint8_t* st0, uin
 #define SEER_GLOAD_B(BQ, T, KS)                                                     \
   {                                                                                 \
     const int t_ = (T) < KT ? (T) : KT - 1;                                         \
-    const char* bk_ = Bb + (size_t)t_ * B_TILE + (KS) * B_SLICE;            \
+    const char* bk_ = Bb + (size_t)(kt0 + t_) * B_TILE + (KS) * B_SLICE;            \
     _Pragma("unroll") for (int j = 0; j < 2; ++j)                                   \
       BQ[j][KS] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const u32x4_t*>(bk_ + b_off[j])); \
   }
@@ -304,6 +306,25 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, uint8_t* st0, uin
 #undef SEER_FLOAD
 #undef SEER_TILE
 #undef SEER_TILE_D
+
+  // ---- one part of a K split: its sums, row-major in the packed column order
+  // of the weight (the epilogue is applied to all parts' sum) -----------------
+  if constexpr (PART) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int row = m0 + i * 32 + fr;
+      if (row < M) {
+        float* prow = sums + (size_t)row * (size_t)p.N + wcol + 4 * fhalf;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4_t*>(prow + 32 * j + 8 * q) =
+                f32x4_t{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+      }
+    }
+    return;
+  }
 
   // ---- epilogue -----------------------------------------------------------
   // The MFMAs take the B fragment as the matrix-core row operand, so tile
@@ -604,7 +625,7 @@ struct Units256 {
   int tiles_m, tiles_mf, tiles_n;
   int nfull, nlast;      // tiles of the full tile rows; half tiles of a short last row
   int full, nsplit;      // whole tiles; halves of the tiles past them
-  __host__ __device__ Units256(int M, int N, int n_units, const int* mtiles) {
+  __device__ Units256(int M, int N, int n_units, const int* mtiles) {
     tiles_m = mtiles ? mtiles[0] : (M + 255) / 256;
     tiles_n = N / 256;
     // A last tile row that holds at most 128 rows runs as single half tiles
@@ -671,8 +692,20 @@ template <int EPI>
 static void launch_epi(const GemmParams& p, hipStream_t s) {
   const int tiles_m = (p.m_ub + 255) / 256, tiles_n = p.N / 256;
   const int tiles = tiles_m * tiles_n;
+  FewRule rule{};
   if (p.n_units > 0 && tiles <= p.n_units) {
-    hipLaunchKernelGGL(gemm_bf16_split_kernel<EPI>, dim3(few_units(p)), dim3(NT), 0, s, p);
+    // a unit of few_tile leaves at most 64 KiB of sums
+    const bool split = p.partial && p.n_units <= kSplitCounters && (size_t)p.n_units * 65536 <= p.partial_bytes;
+    rule = few_rule(FewLaunch{p.m_ub, p.N, p.K, p.n_units, split, EPI == EPI_RESID_PAIR && p.partial, p.partial_bytes});
+  }
+  if (rule.n_runs > 0) {
+    // the last row of a row-tile list runs as whole 256-row tiles
+    const int grid = p.mtiles && rule.grid < p.n_units ? p.n_units : rule.grid;
+    hipLaunchKernelGGL(gemm_bf16_split_kernel<EPI>, dim3(grid), dim3(NT), 0, s, rule.runs, p);
+    if (rule.parts_rows > 0) {
+      const long long groups = (long long)rule.parts_rows * (p.N / 8);
+      hipLaunchKernelGGL(gemm_parts_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s, rule.runs, p);
+    }
   } else {
     // the split last round adds at most n_units / 2 units
     hipLaunchKernelGGL(gemm_bf16_kernel<EPI>, dim3(tiles + (p.n_units > 0 ? p.n_units / 2 : 0)), dim3(NT), 0, s, p);

@@ -2,22 +2,19 @@
 // epilogues of gemm_bf16.hip (included there).
 //
 // With few rows (a cached step, one request, a small model) 256x256 tiles
-// leave most CUs idle, and splitting such tiles over K costs more than it
-// gives: 256 KiB of sums per unit through memory and a second launch.  So a
-// workgroup takes a 128x64 tile (or 128x128) and its four waves a quarter of
-// K each, summed in LDS: no barrier in the loop, enough units to fill the chip,
-// and sums through memory only for a last round, 32 KiB a unit, added by the
-// last unit to arrive in the same launch.
+// leave most CUs idle.  So a workgroup takes a 128x64 tile (or 128x128) and its
+// four waves a quarter of K each, summed in LDS: no barrier in the loop, and
+// where the tiles do not fill the chip K is split further over workgroups, whose
+// sums go through memory, 32 or 64 KiB a unit, added by the last unit to arrive
+// in the same launch.  Where the 128x128 tiles are one round's worth or a little
+// more and K is long, 256x256 tiles split over K with a second launch for the
+// sums load fewer operand bytes a flop and win (few_us has each form's cost).
 //
 // What bounds it: at one tile row the weights from HBM (d 4096, 97 rows: gate/up
-// 201 MB in 55 us, 3.7 TB/s), at small d the launch and one tile's chain, beyond
+// 201 MB in 52 us, 3.9 TB/s), at small d the launch and one tile's chain, beyond
 // a few tile rows the operand loads from L2 (60-75 GB/s a CU; 128x64 tiles load
 // three times the bytes a flop of 256x256 ones), where the larger tiles take
-// over.  Times in us before (256x256 tiles split over K, the sums added
-// by a second kernel) and now, QKV / O / gate-up / down:
-//   d 4096, 97 rows    38 / 28 / 67 / 44  -> 32 / 16 / 52 / 31
-//   d 4096, 890 rows   O and down under a loose rows bound 65 / 165 -> 48 / 111
-//   d 512, 1110 rows   28 / 21 / 28 / 25  -> 6 / 6 / 9 / 9
+// over.
 #pragma once
 
 namespace seer {
@@ -450,67 +447,17 @@ __device__ __forceinline__ void few_tile(const GemmParams& p, uint8_t* st0, uint
   for (int g = 0; g < NJ / 2; ++g) epi[g].apply(p, M, row0, n0 + 64 * g, own[2 * g], own[2 * g + 1]);
 }
 
-// How a launch of 128 x (32 NJ) tiles is cut: whole tiles, and the `rem` tiles
-// of a partly filled last round, whose K is split over S units each.  Whole
-// numbers throughout: the host sizes the grid by the same rule.
-struct FewPlan {
-  int full, rem, S;
-  long long ns;                                     // expected time
-  // round: ns of one round over K = 4096; a split adds base + step S
-  __host__ __device__ FewPlan(int tiles, int ktiles, int units, bool split, int round, int base, int step) {
-    rem = tiles % units;
-    full = tiles - rem;
-    S = 1;
-    if (split && rem > 0 && rem <= kSplitCounters) {
-      S = units / rem;
-      S = S < ktiles / 8 ? S : ktiles / 8;
-      S = S < 1 ? 1 : (S > 16 ? 16 : S);
-    }
-    const long long k = (long long)round * ktiles / 64;
-    long long last = rem > 0 ? k : 0;
-    const long long cut = k / S + base + step * S;
-    if (S > 1 && cut < last) last = cut;
-    else S = 1;
-    ns = k * (full / units) + last;
-  }
-};
-
-// The tile shape of M rows: the one with the least expected time of
-//   128x64 and 128x128 tiles (few_tile), the last round split over K;
-//   256x256 tiles and halves (gemm_tile).
-// The round times and split costs are fits to the times of the three shapes
-// alone, 17 to 2700 rows, d_model 512 to 4096.
-struct FewChoice {
-  FewPlan narrow, wide;
-  Units256 big;
-  int tiles_m;
-  enum { NARROW, WIDE, BIG } shape;
-  __host__ __device__ FewChoice(int M, int N, int K, int units, bool split)
-      : narrow((M + FEW_ROWS - 1) / FEW_ROWS * (N / 64), K / BK, units, split, 25000, 4000, 700),
-        wide((M + FEW_ROWS - 1) / FEW_ROWS * (N / 128), K / BK, units, split, 37000, 12000, 1200),
-        big(M, N, units, nullptr), tiles_m((M + FEW_ROWS - 1) / FEW_ROWS) {
-    const int part = big.nsplit + big.nlast;        // half tiles of a last round
-    const long long big_ns = (85000ll * ((big.full + units - 1) / units) +
-                              (big.full % units == 0 && part > 0 ? 62000 : 0)) * (K / BK) / 64;
-    const bool wide_ok = K / BK % 8 == 0;           // its loop takes two K tiles a wave
-    if (big_ns < narrow.ns && (!wide_ok || big_ns < wide.ns)) shape = BIG;
-    else shape = wide_ok && wide.ns < narrow.ns ? WIDE : NARROW;
-  }
-  __host__ __device__ int units() const {
-    return shape == BIG ? big.full + big.nsplit + big.nlast
-                        : shape == WIDE ? wide.full + wide.rem * wide.S : narrow.full + narrow.rem * narrow.S;
-  }
-};
-
-// Unit u of that plan over the launch's tiles_m x tiles_n tiles.  Whether and
-// how a tile's K is split follows from its place among all tiles, also when
-// only the tiles of a row-tile list are computed, so that a row's result does
-// not depend on the list.
+// Unit u over the launch's tiles_m x tiles_n tiles: whole tiles in full rounds,
+// then the others, their K split over S units each.  Whether and how a tile's K
+// is split follows from its place among all tiles, also when only the tiles of a
+// row-tile list are computed, so that a row's result does not depend on the list.
 template <int EPI, int NJ>
 __device__ __forceinline__ void run_unit_few(const GemmParams& p, uint8_t* st0, uint8_t* st1, uint8_t* st2, uint8_t* st3,
-                                             int* s_last, int M, int tiles_m, const FewPlan& w, int u) {
+                                             int* s_last, int M, int tiles_m, bool k_split, int u) {
   auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };   // keeps the buffer descriptors scalar
-  const int tiles_n = p.N / (32 * NJ);
+  const int tiles_n = p.N / (32 * NJ), tiles = tiles_m * tiles_n;
+  const int full = few_full(p.n_units, tiles), rem = tiles - full;
+  const int splits = k_split ? few_k_splits(p.n_units, rem, p.K / BK) : 1;
   int tm, tn, sp = 0, r = 0, S = 1;
   if (p.mtiles) {
     // first every listed tile, whole or its split 0; then the other splits of
@@ -522,69 +469,127 @@ __device__ __forceinline__ void run_unit_few(const GemmParams& p, uint8_t* st0, 
       raster(xcd_remap(u, listed * tiles_n), listed, tiles_n, tm, tn);
       tm = 2 * p.mtiles[1 + (tm >> 1)] + (tm & 1);
       const int lid = raster_of(tm, tn, tiles_m, tiles_n);
-      if (lid >= w.full) { r = lid - w.full; S = w.S; }
+      if (lid >= full) { r = lid - full; S = splits; }
     } else {
       const int v = u - listed * tiles_n;
-      if (v >= w.rem * (w.S - 1)) return;
-      S = w.S;
-      sp = 1 + v / w.rem;
-      r = v % w.rem;
-      raster(w.full + r, tiles_m, tiles_n, tm, tn);
+      if (v >= rem * (splits - 1)) return;
+      S = splits;
+      sp = 1 + v / rem;
+      r = v % rem;
+      raster(full + r, tiles_m, tiles_n, tm, tn);
       bool found = false;
       for (int k = 0; k < cnt; ++k) found |= p.mtiles[1 + k] == tm >> 1;
       if (!found) return;
     }
-  } else if (u < w.full) {
-    raster(xcd_remap(u, w.full), tiles_m, tiles_n, tm, tn);
+  } else if (u < full) {
+    raster(xcd_remap(u, full), tiles_m, tiles_n, tm, tn);
   } else {
-    if (u >= w.full + w.rem * w.S) return;
+    if (u >= full + rem * splits) return;
     // split-major, so that the units of one XCD walk the same K range
-    const int v = xcd_remap(u - w.full, w.rem * w.S);
-    S = w.S;
-    sp = v / w.rem;
-    r = v - sp * w.rem;
-    raster(w.full + r, tiles_m, tiles_n, tm, tn);
+    const int v = xcd_remap(u - full, rem * splits);
+    S = splits;
+    sp = S > 1 ? v / rem : 0;
+    r = v - sp * rem;
+    raster(full + r, tiles_m, tiles_n, tm, tn);
   }
   const int m0 = tm * FEW_ROWS;
   if (m0 >= M) return;
   // the wide tile's loop takes two K tiles a wave: splits of whole 512-wide runs
   constexpr int RUN = NJ == 2 ? 1 : 8;
   const int runs = p.K / BK / RUN;
-  const int k0 = runs * sp / S * RUN, k1 = runs * (sp + 1) / S * RUN;
+  const int k0 = S > 1 ? runs * sp / S * RUN : 0, k1 = S > 1 ? runs * (sp + 1) / S * RUN : runs * RUN;
   few_tile<EPI, NJ>(p, st0, st1, st2, st3, s_last, uni(M), uni(m0), uni(tn * 32 * NJ), uni(k0), uni(k1), uni(sp), uni(S),
                     uni(r));
 }
 
+// The run of the rule for tiles_m row tiles, 0 (FEW_WHOLE) past the last.
+__device__ __forceinline__ unsigned few_run(const FewRuns& w, int tiles_m) {
+  unsigned run = 0;
+#pragma unroll
+  for (int i = kFewRuns - 1; i >= 0; --i)
+    if (tiles_m <= few_end(w.run[i])) run = w.run[i];
+  return run;
+}
+
 // Launches whose 256x256 tiles (of the rows bound) fill at most one round of
-// the n_units workgroups that run at once; the tile shape follows the real row
+// the n_units workgroups that run at once; the form follows from the real row
 // count, read on the device.
 template <int EPI>
-__global__ __launch_bounds__(NT, 1) void gemm_bf16_split_kernel(GemmParams p) {
+__global__ __launch_bounds__(NT, 1) void gemm_bf16_split_kernel(FewRuns w, GemmParams p) {
   __shared__ __attribute__((aligned(1024))) uint8_t st0[4 * FEW_STAGE];
   __shared__ __attribute__((aligned(1024))) uint8_t st1[4 * FEW_STAGE];
   __shared__ __attribute__((aligned(1024))) uint8_t st2[4 * FEW_STAGE];
   __shared__ __attribute__((aligned(1024))) uint8_t st3[4 * FEW_STAGE];
   __shared__ int s_last;
   const int M = rows_from(p.m_ptr, p.m_ub);
-  const FewChoice c(M, p.N, p.K, p.n_units, p.partial != nullptr);
-  if (c.shape == FewChoice::BIG)
-    run_unit256<EPI>(p, st0, st1, st2, st3, M, Units256(M, p.N, p.n_units, p.mtiles), blockIdx.x);
-  else if (c.shape == FewChoice::WIDE)
-    run_unit_few<EPI, 4>(p, st0, st1, st2, st3, &s_last, M, c.tiles_m, c.wide, blockIdx.x);
-  else
-    run_unit_few<EPI, 2>(p, st0, st1, st2, st3, &s_last, M, c.tiles_m, c.narrow, blockIdx.x);
+  const int tiles_m = (M + FEW_ROWS - 1) / FEW_ROWS;
+  const int u = blockIdx.x;
+  const unsigned run = few_run(w, tiles_m);
+  const int shape = few_form(run);
+  if (__builtin_expect(shape == FEW_WHOLE, 1)) {
+    run_unit256<EPI>(p, st0, st1, st2, st3, M, Units256(M, p.N, p.n_units, p.mtiles), u);
+  } else if (shape == FEW_WIDE) {
+    run_unit_few<EPI, 4>(p, st0, st1, st2, st3, &s_last, M, tiles_m, few_run_splits(run), u);
+  } else if (shape == FEW_NARROW) {
+    run_unit_few<EPI, 2>(p, st0, st1, st2, st3, &s_last, M, tiles_m, few_run_splits(run), u);
+  } else if constexpr (EPI == EPI_RESID_PAIR) {
+    const int parts = few_run_parts(run);
+    // unit u: part u % parts of tile u / parts; gemm_parts_kernel adds the sums
+    const int tm256 = p.mtiles ? p.mtiles[0] : (M + 255) / 256, tiles_n = p.N / 256;
+    if (u >= tm256 * tiles_n * parts) return;
+    const int tile = u / parts, sp = u - tile * parts;
+    const int kts = p.K / BK / parts;
+    int tm, tn;
+    raster(tile, tm256, tiles_n, tm, tn);
+    if (p.mtiles) tm = p.mtiles[1 + tm];
+    gemm_tile<EPI, 256, true>(p, st0, st1, st2, st3, M, tm * 256, tn * 256, kts, sp * kts,
+                              p.partial + (size_t)sp * (size_t)(tiles_m * FEW_ROWS) * (size_t)p.N);
+  }
 }
 
-// The most units a launch can have at any row count up to m_ub.  A surplus
-// workgroup costs about a microsecond of a CU's time (it needs the tile's LDS
-// to start), so the grid is sized by the rule and not by a loose bound.
-static int few_units(const GemmParams& p) {
-  int most = p.mtiles ? p.n_units : 1;             // a list's last row runs as whole 256-row tiles
-  for (int M = 128; M < p.m_ub + 128; M += 128) {
-    const int u = FewChoice(M < p.m_ub ? M : p.m_ub, p.N, p.K, p.n_units, p.partial != nullptr).units();
-    most = u > most ? u : most;
+// The second launch of FEW_PARTS with the residual pair's epilogue: a thread adds
+// 8 columns of the parts in part order and the residual, and stores them.  Exits
+// at once where the rule has another form for the real row count.
+__global__ __launch_bounds__(256) void gemm_parts_kernel(FewRuns w, GemmParams p) {
+  const int M = rows_from(p.m_ptr, p.m_ub);
+  const int tiles_m = (M + FEW_ROWS - 1) / FEW_ROWS;
+  const unsigned run = few_run(w, tiles_m);
+  if (few_form(run) != FEW_PARTS) return;
+  const int parts = few_run_parts(run);
+  const int groups = p.N / 8;
+  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+  int row = (int)(idx / groups);
+  const int col = 8 * (int)(idx - (long long)row * groups);
+  if (p.mtiles) {
+    if ((row >> 8) >= p.mtiles[0]) return;
+    row = p.mtiles[1 + (row >> 8)] * 256 + (row & 255);
   }
-  return most;
+  if (row >= M) return;
+  float v[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = 0.0f;
+  for (int sp = 0; sp < parts; ++sp) {
+    const float* src = p.partial + ((size_t)sp * (size_t)(tiles_m * FEW_ROWS) + (size_t)row) * (size_t)p.N + col;
+    const f32x4_t a = *reinterpret_cast<const f32x4_t*>(src);
+    const f32x4_t b = *reinterpret_cast<const f32x4_t*>(src + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] += a[e];
+      v[4 + e] += b[e];
+    }
+  }
+  auto add = [&](const void* rows) {
+    const u32x4_t r = *reinterpret_cast<const u32x4_t*>(static_cast<const uint16_t*>(rows) + (size_t)row * p.ldr + col);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[2 * e] += __uint_as_float(r[e] << 16);
+      v[2 * e + 1] += __uint_as_float(r[e] & 0xffff0000u);
+    }
+  };
+  add(p.R);
+  add(p.R2);
+  *reinterpret_cast<u32x4_t*>(static_cast<uint16_t*>(p.C) + (size_t)row * p.ldc + col) =
+      u32x4_t{pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])};
 }
 
 }  // namespace seer

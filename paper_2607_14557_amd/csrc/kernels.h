@@ -28,7 +28,7 @@ struct ArgmaxPartial {
   int pad;
 };
 
-// Tiles of a launch whose K can be split (fewer than the CUs / 2).
+// Tiles of a launch whose K can be split over workgroups (at most half the CUs).
 constexpr int kSplitCounters = 256;
 
 // C[M,N] = A[M,K] * B[N,K]^T with a fused epilogue.  M is read on the device
@@ -72,9 +72,10 @@ struct GemmParams {
   // magnitude above fp16's largest finite value
   int* status;
   // bf16, optional: scratch for the fp32 sums of launches of few tiles that
-  // split K (gemm_bf16_split_kernel: at most n_units x 64 KiB), and their
+  // split K (partial_bytes bytes; used where they hold the sums), and their
   // arrival counters (kSplitCounters ints, zero at the launch; both or neither)
   float* partial;
+  size_t partial_bytes;
   int* counters;
   // bf16, optional: the 256-row tiles to compute.  mtiles[0] = their number,
   // mtiles[1 ..] = their indices t (rows 256 t .. 256 t + 255) in increasing

@@ -70,8 +70,8 @@ struct WsLayout {
 };
 
 // bf16 layers: fp32 sums of the GEMMs that split K (launches of few tiles; at
-// most 64 KiB per workgroup of one round of 256 CUs), and at the region's end
-// the arrival counters of the layer's four GEMMs.
+// most one 256x256 fp32 tile per workgroup of one round, 256 CUs x 256 KiB), and
+// at the region's end the arrival counters of the layer's four GEMMs.
 constexpr size_t PART_BYTES = (size_t)64 << 20;
 constexpr size_t COUNTER_BYTES = 4 * seer::kSplitCounters * sizeof(int);
 
@@ -244,6 +244,14 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
   const uint8_t* wb = static_cast<const uint8_t*>(w_packed);
   auto gemm = bf16 ? seer::launch_gemm_bf16 : seer::launch_gemm_f32;
 
+  // the scratch of projection k's K splits
+  auto split_scratch = [&](seer::GemmParams& g, int k) {
+    if (!part) return;
+    g.partial = part;
+    g.partial_bytes = L.part_bytes - COUNTER_BYTES;
+    g.counters = counters + k * seer::kSplitCounters;
+  };
+
   // a NULL entry skips that mark: each record on the stream delays the next
   // launch by a few microseconds, so a caller timing one kernel passes only
   // the two events around it
@@ -263,7 +271,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
   {
     seer::GemmParams g{};
     g.n_units = n_units;
-    g.partial = part; g.counters = counters;
+    split_scratch(g, 0);
     g.A = x_in; g.B = wb + P.qkv * es; g.C = qkv; g.rs = inv1;
     g.m_ptr = m_ptr; g.m_ub = R; g.N = 3 * d; g.K = d;
     g.lda = d; g.ldb = d; g.ldc = 3 * d;
@@ -298,7 +306,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
   {
     seer::GemmParams g{};
     g.n_units = n_units;
-    g.partial = part; g.counters = counters + seer::kSplitCounters;
+    split_scratch(g, 1);
     g.A = o; g.B = wb + P.o * es; g.C = h1; g.R = x_in; g.C2 = h1lo;
     g.m_ptr = m_ptr; g.m_ub = R; g.N = d; g.K = d;
     g.lda = d; g.ldb = d; g.ldc = d; g.ldr = d;
@@ -313,7 +321,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
     if (act_count && seer::launch_zero_i32(act_count, R, stream)) return hip_fail("zero launch");
     seer::GemmParams g{};
     g.n_units = n_units;
-    g.partial = part; g.counters = counters + 2 * seer::kSplitCounters;
+    split_scratch(g, 2);
     g.A = h1; g.C = act; g.rs = inv2; g.cnt = act_count; g.eps = act_eps;
     g.m_ptr = m_ptr; g.m_ub = R; g.K = d; g.lda = d; g.ldb = d; g.ldc = I;
     if (bf16) {
@@ -355,7 +363,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
   {
     seer::GemmParams g{};
     g.n_units = n_units;
-    g.partial = part; g.counters = counters + 3 * seer::kSplitCounters;
+    split_scratch(g, 3);
     g.A = act; g.B = wb + P.dn * es; g.C = x_out; g.R = h1; g.R2 = h1lo;
     g.m_ptr = m_ptr; g.m_ub = R; g.N = d; g.K = I;
     g.lda = I; g.ldb = I; g.ldc = d; g.ldr = d;

@@ -3,8 +3,7 @@ one layer call against its float64 product of the inputs that the call itself
 left in the workspace, so that a stage's error is its output rounding plus its
 fp32 sums.  Row counts at the edges of the 32-row blocks and the 128-row tiles,
 widths whose K is split or not, of whole and of odd runs of K tiles, and the
-three tile shapes; then the detection layer's row-tile list over the same
-forms."""
+forms of a launch; then the detection layer's row-tile list over the same."""
 import math
 
 import numpy as np
@@ -24,7 +23,7 @@ FORMS = [
     (512, 1408, [338, 1110]),                    # 22 K tiles: an odd number a wave
     (512, 1024, [1024, 1110, 2700]),             # wide tiles (gate/up), 256-row tiles at 2700
     (1024, 5632, [385]),
-    (4096, 12288, [97, 1100]),                   # wide tiles whose last round is split
+    (4096, 12288, [97, 640, 1100]),              # the down projection's parts added by a second launch
 ]
 
 
@@ -92,6 +91,7 @@ def test_projections(S, d, I, rows):
     (256, 4096, [700, 300, 650], 10, 20),            # split, tiles dropped
     (512, 1024, [700, 300, 1700], 10, 20),           # 256-row tiles
     (2048, 5632, [270, 300], 30, 20),                # wide tiles
+    (4096, 12288, [600, 500], 30, 20),               # the down projection's parts added by a second launch
 ])
 def test_row_tile_list(S, d, I, lens, off, win):
     """The detection layer with every position of the windows kept (act_eps 0): its listed tiles equal the plain
