@@ -371,7 +371,7 @@ __global__ __launch_bounds__(NT, 1) void attn_few_bf16_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) uint8_t k_lds1[4 * FT];
   __shared__ __attribute__((aligned(1024))) uint8_t v_lds0[4 * FT];
   __shared__ __attribute__((aligned(1024))) uint8_t v_lds1[4 * FT];
-  __shared__ float m_first[QF], m_part[4][QF], l_part[4][QF];
+  __shared__ float m_first[2][QF], m_part[4][QF], l_part[4][QF];
 
   // one XCD takes the query tiles of a head together, which share K and V
   const int gx = gridDim.x;
@@ -513,15 +513,17 @@ __global__ __launch_bounds__(NT, 1) void attn_few_bf16_kernel(AttnParams p) {
       const u32x2_t sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mt), __float_as_uint(mt), false, false);
       return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
     };
-    // The maximum of the first 32 keys is every wave's first reference, so
-    // that a probability is rounded alike whichever wave its key falls to.
+    // The maximum of the first 64 keys (waves 0 and 1) is every wave's first
+    // reference, the one that the 128-query form starts from: a probability is
+    // rounded alike whichever wave or form its key falls to, and 32 keys of
+    // infinite negative score alone leave a finite one.
     if (kt == 0) {
-      if (wv == 0) {
-        m_run = tile_max();
-        if (fhalf == 0) m_first[fr] = m_run;
+      if (wv < 2) {
+        const float top = tile_max();
+        if (fhalf == 0) m_first[wv][fr] = top;
       }
       first_barrier();
-      m_run = m_first[fr];
+      m_run = nk > KF ? fmaxf(m_first[0][fr], m_first[1][fr]) : m_first[0][fr];
     }
     probs();
     if (__any(!(lsum < INFINITY))) {

@@ -96,3 +96,48 @@ def test_attention_forms(S, name, bound):
             worst = max(worst, ((o[u, s] - ref).abs() / tol).max().item())
     log("  largest error over its bound: %.2f" % worst)
     assert worst <= 1.0
+
+
+@pytest.mark.parametrize("bound", ["few", "many"])
+def test_infinite_scores(S, bound):
+    """Cached keys whose first 32 have minus infinity in one dim: where the query is positive there, their scores are
+    minus infinity and they weigh nothing beside the other keys, of the same 64-key tile and of later ones; where it is
+    negative the scores are plus infinity and the output is NaN, as softmax's is."""
+    import torch
+    from paper_2607_14557_amd.runner import SeerStack, dims_for
+    H, T, n = 2, 40, 420
+    d, I = 256, 256
+    ub = T + 7 if bound == "few" else 128 * 128 // H + 128 + T
+    assert ((ub - 1) // 32 + 1) * H <= 256 or bound == "many"
+    log("attention with infinite scores, %s tiles" % bound)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+    f = lambda *s: (torch.randn(*s, device="cuda", generator=gen) * 0.06).bfloat16()
+    W = dict(wq=f(d, d), wk=f(d, d), wv=f(d, d), wo=f(d, d), wg=f(I, d), wu=f(I, d), wd=f(d, I),
+             g1=torch.ones(d, device="cuda"), g2=torch.ones(d, device="cuda"))
+    st = SeerStack(dims_for(d, H, 128, I, "bf16"), 1, ub)
+    st.set_layer(0, W)
+    x = torch.randn(ub, d, device="cuda", generator=gen).bfloat16()
+    kv = torch.cat([f(n, d) * 16, (f(n, d) * 16).to(torch.float16).view(torch.bfloat16)], dim=1).contiguous()
+    kv[:32, :d] = 0
+    kv[:32, 0:d:128] = float("-inf")
+    y = torch.empty_like(x)
+    S.seer_layer_forward_cached(st.dims, st.packed[0], x, y, ub, dev(np.array([0, T])), None, 1, kv,
+                                dev(np.array([0, n])), n, st.workspace)
+    torch.cuda.synchronize()
+    off = S.seer_layer_workspace_offsets(st.dims, ub)
+    qkv = view_ws(st.workspace, off[0], ub, 3 * d, "bf16")[:T].contiguous()
+    o = view_ws(st.workspace, off[1], ub, d, "bf16")[:T].double()
+    q = qkv[:, :d].double()
+    k = torch.cat([kv[32:, :d].double(), qkv[:, d:2 * d].double()])
+    v = torch.cat([kv.view(torch.float16)[32:, d:].double(), qkv.view(torch.float16)[:, 2 * d:].double()])
+    for h in range(H):
+        s = slice(128 * h, 128 * h + 128)
+        good = q[:, 128 * h] > 0
+        assert 5 < int(good.sum()) < T - 5
+        assert bool(torch.isnan(o[~good][:, s]).all()), "head %d: a score of plus infinity" % h
+        pr = torch.softmax(q[good][:, s] @ k[:, s].t().contiguous() / 128 ** 0.5, dim=1)
+        ref, mag = pr @ v[:, s].contiguous(), pr @ v[:, s].abs().contiguous()
+        # half an ulp of the bf16 output, fp16 roundings of the probabilities and their sum, fp32 sums in the exponent
+        err = (o[good][:, s] - ref).abs() / (2.0 ** -8 * ref.abs() + 2.0 ** -9 * mag)
+        assert bool((err <= 1.0).all()), "head %d: %.2f of the bound" % (h, err.max().item())
