@@ -692,24 +692,26 @@ template <int EPI>
 static void launch_epi(const GemmParams& p, hipStream_t s) {
   const int tiles_m = (p.m_ub + 255) / 256, tiles_n = p.N / 256;
   const int tiles = tiles_m * tiles_n;
-  FewRule rule{};
-  if (p.n_units > 0 && tiles <= p.n_units) {
-    // a unit of few_tile leaves at most 64 KiB of sums
-    const bool split = p.partial && p.n_units <= kSplitCounters && (size_t)p.n_units * 65536 <= p.partial_bytes;
-    rule = few_rule(FewLaunch{p.m_ub, p.N, p.K, p.n_units, split, EPI == EPI_RESID_PAIR && p.partial, p.partial_bytes});
-  }
-  if (rule.n_runs > 0) {
-    // the last row of a row-tile list runs as whole 256-row tiles
-    const int grid = p.mtiles && rule.grid < p.n_units ? p.n_units : rule.grid;
-    hipLaunchKernelGGL(gemm_bf16_split_kernel<EPI>, dim3(grid), dim3(NT), 0, s, rule.runs, p);
-    if (rule.parts_rows > 0) {
-      const long long groups = (long long)rule.parts_rows * (p.N / 8);
-      hipLaunchKernelGGL(gemm_parts_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s, rule.runs, p);
+  if constexpr (EPI != EPI_ARGMAX) {                // the LM head runs whole tiles (n_units 0)
+    if (p.n_units > 0 && tiles <= p.n_units) {
+      // a unit of few_tile leaves at most 64 KiB of sums
+      const bool split = p.partial && p.n_units <= kSplitCounters && (size_t)p.n_units * 65536 <= p.partial_bytes;
+      const FewRule rule =
+          few_rule(FewLaunch{p.m_ub, p.N, p.K, p.n_units, split, EPI == EPI_RESID_PAIR && p.partial, p.partial_bytes});
+      if (rule.n_runs > 0) {
+        // the last row of a row-tile list runs as whole 256-row tiles
+        const int grid = p.mtiles && rule.grid < p.n_units ? p.n_units : rule.grid;
+        hipLaunchKernelGGL(gemm_bf16_split_kernel<EPI>, dim3(grid), dim3(NT), 0, s, rule.runs, p);
+        if (rule.parts_rows > 0) {
+          const long long groups = (long long)rule.parts_rows * (p.N / 8);
+          hipLaunchKernelGGL(gemm_parts_kernel, dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s, rule.runs, p);
+        }
+        return;
+      }
     }
-  } else {
-    // the split last round adds at most n_units / 2 units
-    hipLaunchKernelGGL(gemm_bf16_kernel<EPI>, dim3(tiles + (p.n_units > 0 ? p.n_units / 2 : 0)), dim3(NT), 0, s, p);
   }
+  // the split last round adds at most n_units / 2 units
+  hipLaunchKernelGGL(gemm_bf16_kernel<EPI>, dim3(tiles + (p.n_units > 0 ? p.n_units / 2 : 0)), dim3(NT), 0, s, p);
 }
 
 int launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s) {

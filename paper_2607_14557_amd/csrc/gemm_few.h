@@ -49,7 +49,7 @@ struct FewEpilogue {
     const int lane = threadIdx.x & 63, fhalf = lane >> 5;
     int row = row0 + (lane & 31);
     row = row < M ? row : M - 1;                    // rows past M are never stored
-    if constexpr (kScale || kGlu || EPI == EPI_ARGMAX) sc = p.rs[row];
+    if constexpr (kScale || kGlu) sc = p.rs[row];
     if constexpr (EPI == EPI_SCALE_ROPE) pos = p.rope_pos[row];
     if constexpr (kRes) {
       const uint16_t* rb = static_cast<const uint16_t*>(p.R) + (size_t)row * p.ldr + wcol + 8 * fhalf;
@@ -111,34 +111,6 @@ struct FewEpilogue {
       if constexpr (EPI == EPI_SWIGLU_COUNT) {
         nz += __shfl_xor(nz, 32, kWave);
         if (ok && fhalf == 0) atomicAdd(p.cnt + row, nz);
-      }
-    } else if constexpr (EPI == EPI_ARGMAX) {
-      // the lane's columns in increasing order, so a strict > keeps the
-      // smallest column among equal maxima; then the lane pair
-      const int cb = wcol + cq;
-      float m = -INFINITY;
-      int a = cb;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const float v = (j ? a1[e] : a0[e]) * sc;
-          if (v > m) { m = v; a = cb + 32 * j + 8 * (e >> 2) + (e & 3); }
-        }
-      float sum = 0.0f;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sum += __expf((j ? a1[e] : a0[e]) * sc - m);
-      const float m2 = __shfl_xor(m, 32, kWave);
-      const float s2 = __shfl_xor(sum, 32, kWave);
-      const int at2 = __shfl_xor(a, 32, kWave);
-      const float mm = fmaxf(m, m2);
-      const float st = sum * __expf(m - mm) + s2 * __expf(m2 - mm);
-      const int at = (m2 > m || (m2 == m && at2 < a)) ? at2 : a;
-      if (ok && fhalf == 0) {
-        ArgmaxPartial* dst = static_cast<ArgmaxPartial*>(p.C) + (size_t)row * p.ldc + (wcol >> 6);
-        *reinterpret_cast<u32x4_t*>(dst) = u32x4_t{__float_as_uint(mm), __float_as_uint(st), (uint32_t)at, 0u};
       }
     } else {
       // below perm_col1 the two blocks are features (32 h, 64 + 32 h) of one

@@ -18,12 +18,13 @@ pytestmark = pytest.mark.gpu
 BF16, FP16 = 2.0 ** -8, 2.0 ** -11
 # d_model, d_ff, rows
 FORMS = [
-    (256, 4096, [1, 31, 33, 128, 129, 300]),     # narrow tiles, down projection split over K up to eight ways
+    (256, 4096, [1, 31, 33, 128, 129, 300]),     # 128x64 tiles, the down projection's K split eight ways
     (256, 384, [97, 640]),                       # six K tiles: waves with one and with two
     (512, 1408, [338, 1110]),                    # 22 K tiles: an odd number a wave
-    (512, 1024, [1024, 1110, 2700]),             # wide tiles (gate/up), 256-row tiles at 2700
+    (512, 1024, [1024, 1110, 2700]),             # one full round of 128x64 tiles (gate/up), whole tiles beside them
     (1024, 5632, [385]),
-    (4096, 12288, [97, 640, 1100]),              # the down projection's parts added by a second launch
+    (4096, 12288, [97, 450, 640, 1100]),         # 128x128 tiles, split two ways (450, down); parts of 256x256 tiles
+                                                 # added by a second launch (640 and 1100, down)
 ]
 
 
@@ -85,30 +86,31 @@ def test_projections(S, d, I, rows):
     _check("wd", y[:rows], pair + act @ W["wd"], BF16, I)
 
 
-@pytest.mark.parametrize("d,I,lens,off,win", [
-    (512, 1024, [370, 370, 370], 170, 200),          # nine 128-row tiles, all listed
-    (256, 4096, [370, 370, 370], 170, 200),          # the same with the down projection split
-    (256, 4096, [700, 300, 650], 10, 20),            # split, tiles dropped
-    (512, 1024, [700, 300, 1700], 10, 20),           # 256-row tiles
-    (2048, 5632, [270, 300], 30, 20),                # wide tiles
-    (4096, 12288, [600, 500], 30, 20),               # the down projection's parts added by a second launch
+@pytest.mark.parametrize("d,I,lens,off,win,spare", [
+    (512, 1024, [370, 370, 370], 170, 200, 300),     # nine 128-row tiles, all listed
+    (256, 4096, [370, 370, 370], 170, 200, 300),     # the same with the down projection split
+    (256, 4096, [700, 300, 650], 10, 20, 300),       # split, tiles dropped
+    (512, 1024, [700, 300, 1700], 10, 20, 300),
+    (2048, 5632, [270, 300], 30, 20, 300),
+    (4096, 12288, [600, 500], 30, 20, 300),          # 128x128 tiles in a full round and a split one
+    (4096, 12288, [600, 500], 30, 20, 100),          # parts added by a second launch
 ])
-def test_row_tile_list(S, d, I, lens, off, win):
+def test_row_tile_list(S, d, I, lens, off, win, spare):
     """The detection layer with every position of the windows kept (act_eps 0): its listed tiles equal the plain
     layer's bit for bit."""
     import torch
     cu = np.concatenate([[0], np.cumsum(lens)])
     T, B = int(cu[-1]), len(lens)
     log("row-tile list: d %d, d_ff %d, rows %s, %d kept of each" % (d, I, lens, off + win))
-    st, _, x = _layer(S, d, I, T + 300, T)
+    st, _, x = _layer(S, d, I, T + spare, T)
     cud, offd, wind = dev(cu), dev(np.full(B, off)), dev(np.full(B, win))
     ref, y = torch.empty_like(x), torch.empty_like(x)
-    cnt = [torch.empty(T + 300, dtype=torch.int32, device="cuda") for _ in range(2)]
-    st.layer(0, x, ref, cud, None, B, T + 300, 0.0, cnt[0])
+    cnt = [torch.empty(T + spare, dtype=torch.int32, device="cuda") for _ in range(2)]
+    st.layer(0, x, ref, cud, None, B, T + spare, 0.0, cnt[0])
     bnd, keep = (torch.empty(B, dtype=torch.int32, device="cuda") for _ in range(2))
     for _ in range(2):
         y.fill_(77.0)
-        S.seer_layer_forward_detect(st.dims, st.packed[0], x, y, T + 300, cud, B, 0.0, cnt[1], offd, wind,
+        S.seer_layer_forward_detect(st.dims, st.packed[0], x, y, T + spare, cud, B, 0.0, cnt[1], offd, wind,
                                     S.seer_snr_params(3, 100, 3, 5, 3), bnd, keep, st.workspace, st.ws_bytes)
         torch.cuda.synchronize()
         assert bool((keep == win).all())
