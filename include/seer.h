@@ -122,8 +122,9 @@ int seer_prepack_weights(const seer_dims* dims, const seer_layer_weights* src,
  * packed rows (qkv, attention output, post-attention residual, SwiGLU
  * activations and two per-row RMS statistics), plus a 256-byte header and,
  * for bf16 layers, 64 MiB for the fp32 partial sums of projections that split
- * their K dimension (those whose 256x256 output tiles would fill at most a
- * third of the GPU's compute units: few rows, as in prefix-cached steps).
+ * their K dimension and their arrival counters (launches of few rows, whose
+ * 256x256 output tiles fill at most one round of the GPU's compute units, as in
+ * prefix-cached steps).
  *
  * Status word: the int32 at byte 0 of the workspace (for every rows bound).
  * Layer calls only ever set bits in it (atomic OR), so it accumulates over

@@ -611,11 +611,7 @@ int launch_attn_bf16(const AttnParams& p, hipStream_t s) {
   if ((uint64_t)p.rows_ub * 3u * (uint64_t)p.d * 2u >= (1ull << 32)) return -1;
   if (p.cu_kv && !p.kv) return -1;
   const dim3 block(NT);
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return -1;
-  if (few_attention(p.rows_ub, p.B, p.n_heads, p.kv_rows_ub, cus)) {
+  if (few_attention(p.rows_ub, p.B, p.n_heads, p.kv_rows_ub, p.n_units)) {
     const dim3 grid(max_row_tiles(p.rows_ub, p.B, QF), p.n_heads);
     hipLaunchKernelGGL(attn_few_bf16_kernel, grid, block, 0, s, p);
   } else {

@@ -154,6 +154,7 @@ struct AttnParams {
   const void* kv;
   const int* cu_kv;
   int kv_rows_ub;        // bound on cu_kv[B] (0 without a cache)
+  int n_units;           // bf16: CUs
 };
 
 int launch_attn_bf16(const AttnParams& p, hipStream_t s);

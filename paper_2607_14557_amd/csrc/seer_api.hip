@@ -297,7 +297,7 @@ static int layer_forward_impl(const seer_dims* dims, const void* w_packed, const
     a.qkv = qkv; a.out = o; a.cu = cu_seqlens; a.used = seqused; a.B = batch;
     a.d = d; a.n_heads = dims->n_heads; a.head_dim = dims->head_dim; a.rows_ub = R;
     a.scale = 1.0f / sqrtf((float)dims->head_dim);
-    a.kv = kv_cache; a.cu_kv = cu_kv; a.kv_rows_ub = kv_rows_ub;
+    a.kv = kv_cache; a.cu_kv = cu_kv; a.kv_rows_ub = kv_rows_ub; a.n_units = n_units;
     if ((bf16 ? seer::launch_attn_bf16(a, stream) : seer::launch_attn_f32(a, stream)))
       return hip_fail("attention launch");
   }
