@@ -14,7 +14,13 @@
 // 201 MB in 52 us, 3.9 TB/s), at small d the launch and one tile's chain, beyond
 // a few tile rows the operand loads from L2 (60-75 GB/s a CU; 128x64 tiles load
 // three times the bytes a flop of 256x256 ones), where the larger tiles take
-// over.
+// over.  Times in us, 256x256 tiles alone split over K with a second launch or
+// in halves, and now, QKV / O / gate-up / down:
+//   d 4096, 97 rows     38 / 25 / 63 / 43    ->  32 / 18 / 50 / 34
+//   d 4096, 890 rows    87 / 53 / 160 / 101  ->  86 / 43 / 159 / 102; O and down
+//                       under a bound of 2304 rows 65 / 163  ->  43 / 103
+//   d 2048, 1280 rows   34 / 33 / 50 / 48    ->  35 / 22 / 50 / 41
+//   d 512, 1137 rows    26 / 21 / 25 / 23    ->  10 / 10 / 11 / 11
 #pragma once
 
 namespace seer {
